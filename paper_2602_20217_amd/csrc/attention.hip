@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(int M, int hq, int hkv, in
                                                       const int32_t* __restrict__ len,
                                                       const float* __restrict__ kvself,
                                                       bf16_t* ohi, bf16_t* olo, float* of,
-                                                      int ldact, int xmap) {
+                                                      int ldact, int okt, int xmap) {
   constexpr int DPL = HD / 64;
   constexpr int CB = 8;
   __shared__ float s_m[4], s_l[4];
@@ -1197,7 +1197,8 @@ __global__ __launch_bounds__(256) void k_attn_combine(int M, int hq, int hkv, in
     for (int e = 0; e < DPL; ++e) acc[e] = fmaf(vs[d0 + e], w, acc[e]);
   }
   const float inv = 1.0f / lsum;
-  const size_t off = (size_t)r * ldact + (size_t)h * HD + d0;
+  const size_t off =
+      okt ? act_off(r, h * HD + d0, okt) : (size_t)r * ldact + (size_t)h * HD + d0;
   if (of) {
 #pragma unroll
     for (int e = 0; e < DPL; ++e) of[off + e] = acc[e] * inv;
@@ -1212,10 +1213,10 @@ __global__ __launch_bounds__(256) void k_attn_combine(int M, int hq, int hkv, in
     }
     if (DPL == 2) {
       *(uint32_t*)&ohi[off] = hp;
-      *(uint32_t*)&olo[off] = lp;
+      if (olo) *(uint32_t*)&olo[off] = lp;
     } else {
       ohi[off] = (bf16_t)hp;
-      olo[off] = (bf16_t)lp;
+      if (olo) olo[off] = (bf16_t)lp;
     }
   }
 }
@@ -1310,7 +1311,7 @@ void attn_combine(const AttnArgs& a, const float* kvself, Act act_out, hipStream
   KS_LAUNCH((k_attn_combine<HDV, BFV>), grid, dim3(256), 0, st, a.M, a.hq, a.hkv,            \
             span, ngrid, a.q, a.part, a.nsplit, a.len, kvself,                               \
             bf ? (bf16_t*)act_out.hi : nullptr, bf ? (bf16_t*)act_out.lo : nullptr,          \
-            bf ? nullptr : (float*)act_out.hi, act_out.ld, xmap)
+            bf ? nullptr : (float*)act_out.hi, act_out.ld, act_out.kt, xmap)
   if (a.hd == 128) KS_COMB(128, true);
   else KS_COMB(64, false);
 #undef KS_COMB

@@ -88,6 +88,7 @@ int dec_span(const ks_model_desc& d) { return 64 * dec_tiles(d.n_max, d.hkv); }
 constexpr int BAT_TILES = KS_BAT_TILES;
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
+size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 struct Layout {
   size_t rope, x, a1hi, a1lo, a2hi, a2lo, qkv, q, kvself, part, logits, am, top1;
@@ -106,13 +107,14 @@ Layout make_layout(const ks_model_desc& d, const ks_limits& lim) {
   y.cells = lim.cap_max + 1;
   y.DR = y.cells * y.RING;
   y.XR = std::max(y.FR, y.DR);
+  const size_t AR = align16(y.XR);  // activation rows: whole operand tiles
   y.LR = std::max(gam1, PB);
   y.nqkv = (d.hq + 2 * d.hkv) * d.hd;
   y.a2w = std::max(d.hq * d.hd, d.ffn);
   const int ns_dec = (d.n_max + dec_span(d) - 1) / dec_span(d);
   const int ns_bat = attn_nsplit(d.n_max, BAT_TILES);
   const size_t row_part = (size_t)d.hq * ns_bat * (d.hd + 2) * 4;  // bytes per batched row
-  y.PA = (int)std::max<size_t>(PB, std::min<size_t>(PA_MAX, PA_PART_BYTES / row_part));
+  y.PA = (int)std::max<size_t>(PB, std::min<size_t>(PA_MAX, PA_PART_BYTES / row_part)) & ~15;
   y.part_rows = y.PA;
   y.part_elems = std::max((size_t)16 * d.hq * ns_dec, (size_t)y.PA * d.hq * ns_bat) * (d.hd + 2);
   const size_t es = d.dtype == KS_BF16 ? 2 : 4;
@@ -124,10 +126,10 @@ Layout make_layout(const ks_model_desc& d, const ks_limits& lim) {
   };
   y.rope = take((size_t)d.n_max * (d.hd / 2) * 2 * 4);
   y.x = take((size_t)y.XR * d.d * 4);
-  y.a1hi = take((size_t)y.XR * d.d * (es == 4 ? 4 : 2));
-  y.a1lo = take((size_t)y.XR * d.d * 2);
-  y.a2hi = take((size_t)y.XR * y.a2w * (es == 4 ? 4 : 2));
-  y.a2lo = take((size_t)y.XR * y.a2w * 2);
+  y.a1hi = take(AR * d.d * (es == 4 ? 4 : 2));
+  y.a1lo = take(AR * d.d * 2);
+  y.a2hi = take(AR * y.a2w * (es == 4 ? 4 : 2));
+  y.a2lo = take(AR * y.a2w * 2);
   y.qkv = take((size_t)y.XR * y.nqkv * 4);
   y.q = take((size_t)y.XR * d.hq * d.hd * 4);
   y.kvself = take((size_t)y.XR * 2 * d.hkv * d.hd * 4);
@@ -212,6 +214,9 @@ struct ks_ctx {
   }
   Act act1() const { return Act{ws + y.a1hi, ws + y.a1lo, md.d}; }
   Act act2() const { return Act{ws + y.a2hi, ws + y.a2lo, y.a2w}; }
+  // batched bf16 rows: one plane in operand tiles, K columns (float32: as act1 / act2)
+  Act bact1() const { return bf() ? Act{ws + y.a1hi, nullptr, 0, md.d / 32} : act1(); }
+  Act bact2(int K) const { return bf() ? Act{ws + y.a2hi, nullptr, 0, K / 32} : act2(); }
   float* hist_row(int i, int slot) const {
     return at<float>(y.hist) + ((size_t)i * y.RING + slot) * md.d;
   }
@@ -329,12 +334,13 @@ void resid_gemm(ks_ctx* c, int R, int K, Act A, const void* W, float* xout, cons
 void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int32_t* pos,
                const int32_t* len, int max_len, int mode, bool batched, const float* next_gain) {
   const ks_model_desc& d = c->md;
-  const Act a1 = c->act1(), a2 = c->act2();
+  const bool sk = skinny(c, R, batched);
+  const Act a1 = sk ? c->act1() : c->bact1(), a2 = sk ? c->act2() : c->bact2(d.hq * d.hd);
   float* qkv = c->at<float>(c->y.qkv);
   float* q = c->at<float>(c->y.q);
   float* kvs = c->at<float>(c->y.kvself);
   const float* rope = c->at<float>(c->y.rope);
-  if (skinny(c, R, batched)) {
+  if (sk) {
     // without q/k norms and for cache writes, RoPE and the key/value stores
     // are the product's epilogue
     const bool fused = mode == 0 && !d.qk_norm;
@@ -370,10 +376,10 @@ void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int
                 q + (size_t)r0 * d.hq * d.hd, c->kc(l), c->vc(l), len + r0, max_len, tiles, span,
                 attn_rows_per_block(d.hq / d.hkv, batched), c->at<float>(c->y.part), ns};
     PROF(c, KS_KC_ATTN, attn_split(aa, c->st));
-    Act out2 = a2;
-    const size_t off = (size_t)r0 * a2.ld * (c->bf() ? 2 : 4);
+    Act out2 = a2;  // from row r0 (a multiple of 16)
+    const size_t off = a2.kt ? (size_t)r0 * a2.kt * 64 : (size_t)r0 * a2.ld * (c->bf() ? 2 : 4);
     out2.hi = (char*)a2.hi + off;
-    out2.lo = c->bf() ? (char*)a2.lo + (size_t)r0 * a2.ld * 2 : nullptr;
+    out2.lo = a2.lo && c->bf() ? (char*)a2.lo + off : nullptr;
     PROF(c, KS_KC_COMBINE,
          attn_combine(aa, mode == 1 ? kvs + (size_t)r0 * 2 * d.hkv * d.hd : nullptr, out2,
                       c->st));
@@ -384,8 +390,9 @@ void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int
 void mlp_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, bool batched,
               const float* next_gain) {
   const ks_model_desc& d = c->md;
-  const Act a1 = c->act1(), a2 = c->act2();
-  if (skinny(c, R, batched)) {
+  const bool sk = skinny(c, R, batched);
+  const Act a1 = sk ? c->act1() : c->bact1(), a2 = sk ? c->act2() : c->bact2(d.ffn);
+  if (sk) {
     PROF(c, KS_KC_GEMM_GATE_UP,
          gemm_bf16_skinny(normed(c, R, 2 * d.ffn, c->wgu[l], EPI_SWIGLU, nullptr, 0, a2),
                           c->st));
@@ -416,7 +423,7 @@ void sublayer_rows(ks_ctx* c, int i, const float* xin, float* xout, int R, const
 void head_rows(ks_ctx* c, const float* x, int R, float* logits_out, int32_t* am, float* top1,
                bool batched, bool prepped = false, const SampleSpec* ss = nullptr) {
   const ks_model_desc& d = c->md;
-  const Act a1 = c->act1();
+  const Act a1 = c->bact1();
   const int step = logits_out ? R : c->y.LR;
   for (int r0 = 0; r0 < R; r0 += step) {
     const int rr = std::min(step, R - r0);

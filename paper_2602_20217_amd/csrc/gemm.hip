@@ -16,16 +16,18 @@
 // a row's result does not depend on how many rows are in the batch: a verify
 // row and the decode step at the same position produce identical bits.
 //
-// Tiled path (batched rows of the selection DP and of prefill): 128 x 256
-// workgroup tiles of eight 64 x 64 wave tiles of 16x16x32 MFMAs over single
-// bf16 activations, operands staged through a three-stage LDS ring by direct
-// global-to-LDS loads; K is split over workgroups when the row count leaves
-// CUs idle (factor from a cost model of resident rounds and partial traffic),
-// and the float32 partials are summed in split order.
+// Batched path (rows of the selection DP and of prefill): single bf16
+// activations in the weights' tile layout, both operands staged through LDS by
+// direct global-to-LDS loads of whole 1 KiB tiles; workgroup tiles of 128 x 128
+// to 256 x 256, eight waves in two groups that alternate between matrix
+// instructions and operand traffic.  The K sum is cut into parts by the sizes
+// alone; the parts run in workgroups of their own or one after the other in one,
+// and are added in order either way.
 #include "ks_internal.h"
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 namespace ks {
 
@@ -446,151 +448,316 @@ void gemm_bf16_skinny(const GemmArgs& g, hipStream_t st) {
   else launch_skinny<KS_SK_WIDE>(g, st);
 }
 
-// ------------------------------------------------------------------- tiled
-// Batched rows (prefill chunks, selection DP).  Workgroup tile 16 WM NWM rows x
-// 16 NWN WN columns, NWM x NWN waves with 16 WM x 16 WN wave tiles (WM x WN
-// MFMAs per k step).
-// A 32-wide k step of the workgroup is WM NWM + NWN WN operand tiles of 1 KiB, each
-// laid out in LDS in MFMA register order (lane l at byte 16 l: row l % 16,
-// k 8 (l / 16)..), so every fragment read is one conflict-free 16-byte read.
-// The tiles travel with direct global-to-LDS loads (one 1 KiB load per tile:
-// lane l fetches row l % 16, k chunk l / 16 of A, or 16 bytes of the packed W
-// tile, which is already in that order), ST - 1 steps ahead of the arithmetic
-// in a ring of ST stages: one barrier per step and no staging registers.
-// Rows past M and tiles past N read clamped (valid) addresses; their results
-// are never stored.  Workgroups that share a weight tile get consecutive
-// logical ids on the same XCD.  Split-K (SK > 1): workgroup (.., ks) adds up
-// k steps [ks KT / SK, (ks + 1) KT / SK) and stores float32 partials
-// part[ks][M][N]; gemm_splitk_reduce adds them in split order.
-#ifndef KS_TILED_WPE
-#define KS_TILED_WPE 1  // waves per SIMD the register budget must allow
-#endif
+// ----------------------------------------------------------------- batched
 __device__ constexpr int vmcnt_imm(int n) {
   // s_waitcnt immediate: vmcnt = n, expcnt and lgkmcnt not waited for
   return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14);
 }
 
-template <int EPI, int ST, int WM, int WN, int NWM, int NWN>
-__global__ __launch_bounds__(64 * NWM * NWN) __attribute__((amdgpu_waves_per_eu(KS_TILED_WPE)))
-void k_gemm_tiled(int M, int N, int K,
-                                                    const bf16_t* __restrict__ A, int lda,
-                                                    const bf16_t* __restrict__ Wp, float* out,
-                                                    int ldo, const float* res, int ldres,
-                                                    bf16_t* ohi, bf16_t* olo, int ldact, int MB,
-                                                    int NB, int SK, float* __restrict__ part) {
-  constexpr int NWV = NWM * NWN;  // waves: NWM along M, NWN along N
-  constexpr int PA = NWM * WM;    // A pieces per step: 16 WM NWM rows
-  constexpr int PB = NWN * WN;   // W pieces per step: 16 NWN WN columns
-  constexpr int PPW = (PA + PB) / NWV;
-  static_assert((PA + PB) % NWV == 0, "pieces split evenly over the waves");
-  __shared__ __align__(16) bf16_t Sg[ST][(PA + PB) * 512];
-  const int KT = K >> 5;
-  const int NT = N >> 4;
-  // XCD-aware logical block id (blocks are dealt round-robin over 8 XCDs)
+// Batched rows (prefill chunks, selection DP).  Workgroup tile 64 RI x
+// 64 (C0 + C1), eight waves (2 x 4).  A k step of 64 is four blocks in LDS, made
+// of 1 KiB operand tiles (16 rows x 32 k) in MFMA register order as they lie in
+// memory: the two row halves of A (2 RI row tiles each) and two column parts of
+// W (4 C0 and 4 C1 column tiles); wave (wm, wn) owns RI row tiles of each A half
+// and C0 + C1 column tiles, so its tile is four quadrants of 2 RI C matrix
+// instructions per step.  Both steps of a two-stage ring are in use; a block is
+// refilled with step k + 2 as soon as its last reader of step k is past, so
+// loads run six phases ahead and no wait ever drains them.
+//
+// A step is four phases: [read the quadrant's new operands, request one block of
+// step k + 2, wait for those reads and for the block needed next; barrier;
+// matrix instructions; barrier].  The four waves of the upper row half (one
+// per SIMD) run one segment ahead of the other four, so on every SIMD one wave
+// issues matrix instructions while the other moves operands.
+//   phase 0: reads A half 0 of step k        requests W part 0   A0 W0
+//   phase 1: reads W part 1                  requests A half 0   A0 W1
+//   phase 2: reads A half 1                  requests W part 1   A1 W1
+//   phase 3: reads W part 0 of step k + 1    requests A half 1   A1 W0
+// A block's refill is requested at least two segments after its reads in the
+// leading group and one after those in the trailing group, which waited for
+// them before the barrier in between.  Tiles past the last re-read the last
+// one (valid addresses, never used), so the count of loads in flight is the
+// same in every phase.  The W fragment is the first operand: a lane then holds
+// four consecutive columns of one row.
+//
+// A result is the sum, in order, of P partial sums over the parts
+// [p KT / P, (p + 1) KT / P) of the 32-wide k tiles, k ascending inside a part
+// (P from gemm_parts).  SPLIT: one workgroup per part stores its float32 sums to
+// part[p][M][N] for k_splitk_reduce.  FOLD: the workgroup walks all parts and
+// adds each to a second set of accumulators where it ends, with no break in the
+// stream of loads.  Tile shape and mode change no bit of the result.
+//
+// What bounds it: operand traffic into LDS, then the matrix units' clock.  At
+// 4096 rows of the gate/up shape (256 x 256 tiles, seven full rounds) it takes
+// 645 us = 1.49 PFLOP/s; without its loads 529-564 us.  With A row-major (each
+// load 16 rows x 64 bytes) the same kernel took 701 us; 128 x 256 tiles in a
+// three-stage ring with one barrier per step took 975 us row-major, 819 us in
+// operand tiles.  At 512 and 1225 rows: 150 -> 101 us and 321 -> 244-273 us.
+enum { MODE_ONE = 0, MODE_SPLIT = 1, MODE_FOLD = 2 };
+template <int EPI, int MODE, int RI, int C0, int C1>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_wide(
+    int M, int N, int K, const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, float* out,
+    int ldo, const float* res, int ldres, bf16_t* ohi, int okt, int MB, int NB, int P, int vec,
+    float* __restrict__ part) {
+  constexpr int GM = 8;  // row tiles that share column tiles (4, 8, 16: within 2%)
+  constexpr int CT = C0 + C1;
+  constexpr int NA = RI > 2 ? 2 : 1, N0 = C0, N1 = C1;  // loads of a wave per block
+  constexpr int NS = 2 * NA + N0 + N1;                   // and per step
+  constexpr int EA = 4 * RI * 512;                       // elements of an A block
+  constexpr int E0 = 8 * C0 * 512, E1 = 8 * C1 * 512;
+  constexpr int OA[2] = {0, EA}, OW[2] = {2 * EA, 2 * EA + E0};
+  __shared__ __align__(16) bf16_t Sg[2][2 * EA + E0 + E1];  // by step parity
+  const int KT = K >> 5, NT = N >> 4, MT = (M + 15) >> 4;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  // logical id: consecutive on one XCD (blocks are dealt round-robin over 8);
+  // GM row tiles by all column tiles in turn, so the tiles that run together on
+  // an XCD share rows and columns
   const int nblk = gridDim.x;
-  const int bid = blockIdx.x;
-  int lb = bid;
-  if ((nblk & 7) == 0) lb = (bid & 7) * (nblk >> 3) + (bid >> 3);
-  const int mb = lb % MB, nb = (lb / MB) % NB, ks = lb / (MB * NB);
-  const int m0 = mb * 16 * WM * NWM, nt0 = nb * PB;
-  const int kb = (ks * KT) / SK, nk = ((ks + 1) * KT) / SK - kb;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % NWM, wn = wave / NWM;
+  int lb = blockIdx.x;
+  if ((nblk & 7) == 0) lb = (lb & 7) * (nblk >> 3) + (lb >> 3);
+  const int ks = MODE == MODE_SPLIT ? lb / (MB * NB) : 0;
+  lb -= ks * (MB * NB);
+  const int grp = lb / (GM * NB), gm = min(GM, MB - grp * GM);
+  lb -= grp * GM * NB;
+  const int mb = grp * GM + lb % gm, nb = lb / gm;
+  const int mt0 = mb * 4 * RI, nt0 = nb * 4 * CT;
+  // 32-wide k tiles [kb, kb + nkt) in nk steps of two (the last may hold one)
+  const int kb = MODE == MODE_SPLIT ? (ks * KT) / P : 0;
+  const int nkt = (MODE == MODE_SPLIT ? ((ks + 1) * KT) / P : KT) - kb;
+  const int nk = (nkt + 1) >> 1;
 
-  // wave w moves pieces PPW w .. + PPW - 1 of every step: pieces 0..PA-1 are A
-  // tiles (rows m0 + 16 p ..), the rest W tiles nt0 + p - PA
-  const bf16_t* src[PPW];
-  int adv[PPW];  // elements per k step
+  // pieces (1 KiB operand tiles) of this wave: of a two-load block tile `wave`,
+  // both k tiles; of a one-load block tile wave / 2, k tile wave % 2 (a block of
+  // 6 row tiles: two waves repeat the last tile)
+  const char* ab = (const char*)(A + ((size_t)mt0 * KT + kb) * 512);
+  const char* wb = (const char*)(Wp + ((size_t)nt0 * KT + kb) * 512);
+  const int ta = NA == 2 ? min(wave, 2 * RI - 1) : wave >> 1;
+  const int t0 = N0 == 2 ? wave : wave >> 1, t1 = N1 == 2 ? wave : wave >> 1;
+  uint32_t ofs[4];
+  ofs[0] = (uint32_t)min(ta, MT - 1 - mt0) * KT * 1024;
+  ofs[1] = (uint32_t)min(2 * RI + ta, MT - 1 - mt0) * KT * 1024;
+  ofs[2] = (uint32_t)min(t0, NT - 1 - nt0) * KT * 1024;
+  ofs[3] = (uint32_t)min(4 * C0 + t1, NT - 1 - nt0) * KT * 1024;
+  auto ask = [&](int k, auto blk_) {  // request block A0, A1, W0, W1 (0..3) of step k
+    constexpr int blk = decltype(blk_)::value;
+    constexpr int n = blk < 2 ? NA : (blk == 2 ? N0 : N1);
+    const int tile = blk < 2 ? ta : (blk == 2 ? t0 : t1);
+    bf16_t* dst = &Sg[k & 1][(blk < 2 ? OA[blk & 1] : OW[blk & 1]) +
+                             (n == 2 ? 2 * tile : wave) * 512];
 #pragma unroll
-  for (int q = 0; q < PPW; ++q) {
-    const int pc = PPW * wave + q;
-    if (pc < PA) {
-      const int row = min(m0 + 16 * pc + (lane & 15), M - 1);
-      src[q] = A + (size_t)row * lda + (size_t)kb * 32 + (lane >> 4) * 8;
-      adv[q] = 32;
-    } else {
-      const int nt = min(nt0 + pc - PA, NT - 1);
-      src[q] = Wp + ((size_t)nt * KT + kb) * 512 + lane * 8;
-      adv[q] = 512;
-    }
-  }
-  auto issue = [&](int step, int buf) {
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-      const bf16_t* s_ = src[q] + (size_t)step * adv[q];
+    for (int kt = 0; kt < n; ++kt)
       __builtin_amdgcn_global_load_lds(
-          (const void*)s_,
-          (__attribute__((address_space(3))) void*)&Sg[buf][(PPW * wave + q) * 512], 16, 0, 0);
+          (const void*)((blk < 2 ? ab : wb) +
+                        (size_t)min(2 * k + (n == 2 ? kt : wave & 1), nkt - 1) * 1024 + ofs[blk] +
+                        lane * 16),
+          (__attribute__((address_space(3))) void*)(dst + kt * 512), 16, 0, 0);
+  };
+  typedef std::integral_constant<int, 0> A0;
+  typedef std::integral_constant<int, 1> A1;
+  typedef std::integral_constant<int, 2> W0;
+  typedef std::integral_constant<int, 3> W1;
+  bf16x8 a[RI][2], w0[2][C0][2], w1[C1][2];
+  auto rd_a = [&](int k, int h) {
+    const bf16_t* s = &Sg[k & 1][OA[h] + wm * RI * 1024 + lane * 8];
+#pragma unroll
+    for (int i = 0; i < RI; ++i)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) a[i][kt] = ld_frag(s + (2 * i + kt) * 512);
+  };
+  auto rd_w0 = [&](int k, bf16x8 (&w)[C0][2]) {
+    const bf16_t* s = &Sg[k & 1][OW[0] + wn * C0 * 1024 + lane * 8];
+#pragma unroll
+    for (int t = 0; t < C0; ++t)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) w[t][kt] = ld_frag(s + (2 * t + kt) * 512);
+  };
+  auto rd_w1 = [&](int k) {
+    const bf16_t* s = &Sg[k & 1][OW[1] + wn * C1 * 1024 + lane * 8];
+#pragma unroll
+    for (int t = 0; t < C1; ++t)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) w1[t][kt] = ld_frag(s + (2 * t + kt) * 512);
+  };
+  f32x4 acc[2][RI][CT];  // [row half][row tile][column tile, part 0 first]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < RI; ++i)
+#pragma unroll
+      for (int t = 0; t < CT; ++t) acc[h][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 tot[MODE == MODE_FOLD ? 2 : 1][MODE == MODE_FOLD ? RI : 1][MODE == MODE_FOLD ? CT : 1];
+  if constexpr (MODE == MODE_FOLD) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < RI; ++i)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) tot[h][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto barrier = [] {
+    __asm__ volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __asm__ volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the phase's wait (its LDS reads are in, all but the newest loads have
+  // landed), barrier, matrix instructions, barrier
+  // fold: -1 no part ends in this step, 0 / 1 before its first / second k tile
+  auto mma = [&](auto hm_, auto wait_, auto part_, auto& w, bool second, int fold) {
+    constexpr int hm = decltype(hm_)::value, c0 = decltype(part_)::value ? C0 : 0;
+    constexpr int C = decltype(part_)::value ? C1 : C0, n = decltype(wait_)::value;
+    auto ktile = [&](int kt) {
+      if (MODE == MODE_FOLD && fold == kt) {
+#pragma unroll
+        for (int i = 0; i < RI; ++i)
+#pragma unroll
+          for (int t = 0; t < C; ++t) {
+            tot[hm][i][c0 + t] += acc[hm][i][c0 + t];
+            acc[hm][i][c0 + t] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+      }
+#pragma unroll
+      for (int i = 0; i < RI; ++i)
+#pragma unroll
+        for (int t = 0; t < C; ++t)
+          acc[hm][i][c0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][kt], a[i][kt],
+                                                                       acc[hm][i][c0 + t], 0, 0, 0);
+    };
+    __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | ((n >> 4) << 14));
+    barrier();
+    __builtin_amdgcn_s_setprio(1);
+    ktile(0);
+    if (second) ktile(1);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+  };
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    ask(k, W0{});
+    ask(k, A0{});
+    ask(k, W1{});
+    ask(k, A1{});
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(NS));
+  barrier();
+  rd_w0(0, w0[0]);
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  barrier();
+  if (wm) barrier();
+  int ending = 0, ends = MODE == MODE_FOLD ? KT / P : 0;  // the part whose end is next
+  auto step = [&](int k, auto par) {
+    constexpr int p = decltype(par)::value;
+    std::integral_constant<int, NS + NA + N0> wait0;
+    std::integral_constant<int, NS + NA + N1> wait1;
+    std::integral_constant<int, 0> I0;
+    std::integral_constant<int, 1> I1;
+    const bool second = 2 * k + 1 < nkt;
+    const int fold = MODE == MODE_FOLD && (ends >> 1) == k ? ends & 1 : -1;
+    if (fold >= 0) {
+      ++ending;
+      ends = ((ending + 1) * KT) / P;  // the last part's end is past the last step
+    }
+    rd_a(k, 0);
+    ask(k + 2, W0{});
+    mma(I0, wait0, I0, w0[p], second, fold);
+    rd_w1(k);
+    ask(k + 2, A0{});
+    mma(I0, wait0, I1, w1, second, fold);
+    rd_a(k, 1);
+    ask(k + 2, W1{});
+    mma(I1, wait1, I1, w1, second, fold);
+    rd_w0(k + 1, w0[p ^ 1]);
+    ask(k + 2, A1{});
+    mma(I1, wait1, I0, w0[p], second, fold);
+  };
+  for (int k = 0; k < nk; k += 2) {
+    step(k, std::integral_constant<int, 0>{});
+    if (k + 1 < nk) step(k + 1, std::integral_constant<int, 1>{});
+  }
+  if (!wm) barrier();
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the re-read steps have landed too
+
+  if constexpr (MODE == MODE_FOLD) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < RI; ++i)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[h][i][t] = tot[h][i][t] + acc[h][i][t];
+  }
+  float* pk = part + (size_t)ks * M * N;
+  auto put = [&](float* dst, f32x4 v) {  // vec: dst is 16-byte aligned
+    if (vec) {
+      *(f32x4*)dst = v;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) dst[u] = v[u];
     }
   };
 #pragma unroll
-  for (int s = 0; s < ST - 1; ++s)
-    if (s < nk) issue(s, s);
-
-  f32x4 acc[WM][WN];
+  for (int hm = 0; hm < 2; ++hm)
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int t = 0; t < WN; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int it = 0; it < nk; ++it) {
-    // step it has landed once at most the ST - 2 later steps are in flight.
-    // The barrier then needs no memory fence (a fence would wait for every
-    // step in flight): this wave's tile loads for step it are counted down
-    // above, and its LDS reads of the stage refilled next were consumed by
-    // the previous step's matrix instructions.
-    if (it + ST - 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(PPW * (ST - 2)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __builtin_amdgcn_s_barrier();
-    __asm__ volatile("" ::: "memory");
-    if (it + ST - 1 < nk) issue(it + ST - 1, (it + ST - 1) % ST);
-    const bf16_t* Sb = Sg[it % ST];
-    bf16x8 a[WM], b[WN];
-#pragma unroll
-    for (int i = 0; i < WM; ++i) a[i] = ld_frag(&Sb[(WM * wm + i) * 512 + lane * 8]);
-#pragma unroll
-    for (int t = 0; t < WN; ++t) b[t] = ld_frag(&Sb[(PA + WN * wn + t) * 512 + lane * 8]);
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int t = 0; t < WN; ++t)
-        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[t], acc[i][t], 0, 0, 0);
-  }
-
-  const int mw = m0 + wm * 16 * WM;
-  const int nw = nt0 + wn * WN;
-  float* pk = part + (size_t)ks * M * N;
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int m = mw + i * 16 + 4 * (lane >> 4) + v;
+    for (int i = 0; i < RI; ++i) {
+      const int mt = mt0 + (2 * hm + wm) * RI + i;
+      const int m = mt * 16 + (lane & 15);
+      if (m >= M) continue;
       if (EPI == EPI_SWIGLU) {
+        // rows 0..7 of a W tile are gates (lanes 0..31), 8..15 ups (lanes
+        // 32..63): exchanging halves between two tiles gives every lane four
+        // gates and their ups (of a single tile: the lower lanes)
+        auto store = [&](int nt, bool ok, f32x4 x, f32x4 y) {
+          float s4[4];
 #pragma unroll
-        for (int t = 0; t < WN; ++t) {
-          const float up = __shfl(acc[i][t][v], (lane & 48) | ((lane + 8) & 15));
-          if (m >= M || nw + t >= NT || (lane & 15) >= 8) continue;
-          const int c = (nw + t) * 8 + (lane & 15);
-          store_split(ohi, olo, (size_t)m * ldact + c, silu_mul(acc[i][t][v], up));
-        }
-      } else {
-        if (m >= M) continue;
-#pragma unroll
-        for (int t = 0; t < WN; ++t) {
-          if (nw + t >= NT) continue;
-          const int n = (nw + t) * 16 + (lane & 15);
-          float sv = acc[i][t][v];
-          if (SK > 1) {
-            pk[(size_t)m * N + n] = sv;
+          for (int v = 0; v < 4; ++v) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[v]),
+                                                             __float_as_uint(y[v]), false, false);
+            s4[v] = silu_mul(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+          }
+          if (!ok) return;
+          const int c = nt * 8 + 4 * ((lane >> 4) & 1);
+          *(uint2*)(ohi + act_off(m, c, okt)) =
+              make_uint2((uint32_t)f2bf(s4[0]) | ((uint32_t)f2bf(s4[1]) << 16),
+                         (uint32_t)f2bf(s4[2]) | ((uint32_t)f2bf(s4[3]) << 16));
+        };
+        auto part_out = [&](int ntp, auto c0_, auto n_) {
+          constexpr int c0 = decltype(c0_)::value, n = decltype(n_)::value;
+          if constexpr (n == 2) {
+            const int nt = ntp + (lane >> 5);
+            store(nt, nt < NT, acc[hm][i][c0], acc[hm][i][c0 + 1]);
           } else {
-            if (EPI == EPI_RESID) sv += res[(size_t)m * ldres + n];
-            out[(size_t)m * ldo + n] = sv;
+            store(ntp, lane < 32 && ntp < NT, acc[hm][i][c0], acc[hm][i][c0]);
+          }
+        };
+        part_out(nt0 + wn * C0, std::integral_constant<int, 0>{}, std::integral_constant<int, C0>{});
+        part_out(nt0 + 4 * C0 + wn * C1, std::integral_constant<int, C0>{},
+                 std::integral_constant<int, C1>{});
+      } else {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const int nt = nt0 + (t < C0 ? wn * C0 + t : 4 * C0 + wn * C1 + t - C0);
+          if (nt >= NT) continue;
+          const int n = nt * 16 + 4 * (lane >> 4);
+          f32x4 v = acc[hm][i][t];
+          if (MODE == MODE_SPLIT) {
+            *(f32x4*)(pk + (size_t)m * N + n) = v;
+          } else {
+            if (EPI == EPI_RESID) {
+              const float* r = res + (size_t)m * ldres + n;
+              if (vec) {
+                v = *(const f32x4*)r + v;
+              } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = r[u] + v[u];
+              }
+            }
+            put(out + (size_t)m * ldo + n, v);
           }
         }
       }
     }
-  }
 }
 
 // out[m][n] = (res[m][n] +) sum over ks in order of part[ks][m][n]; N % 4 == 0
@@ -629,30 +796,28 @@ static int compute_units() {
   return n;
 }
 
-// Split-K factor (1..8) of a tiled product, by a cost model fitted on MI355X
-// to the 128 x 256 tile at the Llama-8B product shapes (400..1225 rows, every
-// factor 1..6 timed): one k step takes about 0.57 us while a workgroup has its
-// CU to itself and 0.97 us while two share it (the CU's matrix and LDS
-// throughput is then split, so the pair gains only ~15%); workgroups beyond
-// the resident set run in further rounds; SK > 1 adds a launch and SK + 2
-// float32 M x N planes of traffic (partials written and read, output) at
-// about 4.5 TB/s.  The model picks the measured best factor, or one within
-// 1 us of it, at every timed shape; split count 1 is kept when the partials
-// would not fit the caller's buffer.
-static int splitk_factor(const GemmArgs& g, int tiles, int KT, int lds_kib) {
+// Parts of the K sum of a product over `rows` rows (see k_gemm_wide).  They set
+// the result's bits, so they follow the sizes alone and are kept apart from the
+// tile shape and from how many rows a launch holds: a prefill pass over several
+// chunks, or another tile, gives the bits of one chunk at a time.  The count
+// comes from a cost model of 128 x 256 tiles, two workgroups per CU, that splits
+// K while the rows leave CUs idle.
+static int gemm_parts(const GemmArgs& g) {
   constexpr double T_ALONE = 0.57, T_SHARED = 0.97, T_LAUNCH = 3.0, BYTES_PER_US = 4.5e6;
   if (g.epi == EPI_SWIGLU || !g.part) return 1;
+  const int rows = g.part_rows ? g.part_rows : g.M, KT = g.K / 32;
+  const int tiles = ((rows + 127) / 128) * ((g.N / 16 + 15) / 16);
   const int cus = compute_units();
-  const int resident = cus * std::max(1, 160 / lds_kib);
+  const int resident = 2 * cus;
   double best = 0.0;
   int best_sk = 1;
   for (int sk = 1; sk <= 8; ++sk) {
-    if (sk > 1 && ((size_t)sk * g.M * g.N * 4 > g.part_bytes || KT / sk < 8)) break;
+    if (sk > 1 && ((size_t)sk * rows * g.N * 4 > g.part_bytes || KT / sk < 8)) break;
     const int steps = (KT + sk - 1) / sk;
     double t = 0.0;
     for (long left = (long)tiles * sk; left > 0; left -= resident)
       t += steps * (std::min<long>(left, resident) > cus ? T_SHARED : T_ALONE);
-    if (sk > 1) t += T_LAUNCH + (sk + 2.0) * g.M * (double)g.N * 4.0 / BYTES_PER_US;
+    if (sk > 1) t += T_LAUNCH + (sk + 2.0) * rows * (double)g.N * 4.0 / BYTES_PER_US;
     if (sk == 1 || t < best) {
       best = t;
       best_sk = sk;
@@ -661,62 +826,99 @@ static int splitk_factor(const GemmArgs& g, int tiles, int KT, int lds_kib) {
   return best_sk;
 }
 
-template <int ST, int WM, int WN, int NWM, int NWN>
-static void launch_tiled(const GemmArgs& g, hipStream_t st) {
-  const int NT = g.N / 16;
-  const int KT = g.K / 32;
-  const int MB = (g.M + 16 * WM * NWM - 1) / (16 * WM * NWM);
-  const int NB = (NT + NWN * WN - 1) / (NWN * WN);
-  const int SK = splitk_factor(g, MB * NB, KT, ST * (WM * NWM + NWN * WN));
-  dim3 grid(MB * NB * SK);
-  const bf16_t* A = (const bf16_t*)g.A.hi;
-  const bf16_t* W = (const bf16_t*)g.W;
-  if (g.epi == EPI_SWIGLU)
-    KS_LAUNCH((k_gemm_tiled<EPI_SWIGLU, ST, WM, WN, NWM, NWN>), grid, dim3(64 * NWM * NWN), 0, st, g.M, g.N,
-              g.K, A, g.A.ld, W, g.out, g.ldo, g.res, g.ldres, (bf16_t*)g.act_out.hi,
-              (bf16_t*)g.act_out.lo, g.act_out.ld, MB, NB, 1, g.part);
-  else if (g.epi == EPI_RESID)
-    KS_LAUNCH((k_gemm_tiled<EPI_RESID, ST, WM, WN, NWM, NWN>), grid, dim3(64 * NWM * NWN), 0, st, g.M, g.N, g.K,
-              A, g.A.ld, W, g.out, g.ldo, g.res, g.ldres, nullptr, nullptr, 0, MB, NB,
-              SK, g.part);
-  else
-    KS_LAUNCH((k_gemm_tiled<EPI_STORE, ST, WM, WN, NWM, NWN>), grid, dim3(64 * NWM * NWN), 0, st, g.M, g.N, g.K,
-              A, g.A.ld, W, g.out, g.ldo, g.res, g.ldres, nullptr, nullptr, 0, MB, NB,
-              SK, g.part);
-  if (SK > 1) {
-    const size_t n4 = (size_t)g.M * (g.N / 4);
-    dim3 rg((unsigned)((n4 + 255) / 256));
-    if (g.epi == EPI_RESID)
-      KS_LAUNCH(k_splitk_reduce<EPI_RESID>, rg, dim3(256), 0, st, g.M, g.N, SK, g.part,
-                g.out, g.ldo, g.res, g.ldres);
-    else
-      KS_LAUNCH(k_splitk_reduce<EPI_STORE>, rg, dim3(256), 0, st, g.M, g.N, SK, g.part,
-                g.out, g.ldo, g.res, g.ldres);
+// Tile shapes of k_gemm_wide and their cost on MI355X, fitted to 11 row counts
+// (100..4096) x the four Llama-8B product shapes x every split factor: us per
+// k step of 64 while more than one workgroup per CU (at most 80 KiB of LDS) or
+// every CU is busy (full) and in a last round of at most one workgroup per CU
+// (alone), and us per round.  A launch costs WIDE_LAUNCH, a split WIDE_SPLIT and
+// P + 2 float32 planes at WIDE_BYTES per us; folding the parts in the workgroup
+// costs no traffic but needs a second set of accumulators, so only the 128 x 256
+// tile does it.
+struct WideShape {
+  int ri, c0, c1;
+  double full, alone, round;
+};
+static constexpr WideShape WIDE[] = {
+    {2, 1, 1, 0.916, 0.609, 0.67},
+    {2, 2, 2, 0.844, 0.675, 2.27},
+    {3, 2, 2, 1.100, 0.836, 3.35},
+    {4, 2, 2, 1.375, 1.023, 4.55},
+};
+struct WidePick {
+  int shape, mode;
+};
+static WidePick wide_pick(const GemmArgs& g, int P) {
+  constexpr double WIDE_LAUNCH = 4.8, WIDE_SPLIT = 2.2, WIDE_BYTES = 4.9e6;
+  const int cus = compute_units();
+  WidePick best{-1, MODE_ONE};
+  double tb = 0.0;
+  for (int i = 0; i < 4; ++i) {
+    const WideShape& w = WIDE[i];
+    const long tiles = (long)((g.M + 64 * w.ri - 1) / (64 * w.ri)) *
+                       ((g.N / 16 + 4 * (w.c0 + w.c1) - 1) / (4 * (w.c0 + w.c1)));
+    const int resident = cus * (16 * w.ri + 16 * (w.c0 + w.c1) <= 80 ? 2 : 1);
+    for (int mode = P > 1 ? MODE_SPLIT : MODE_ONE; mode <= (P > 1 ? MODE_FOLD : MODE_ONE); ++mode) {
+      if (mode == MODE_SPLIT && (size_t)P * g.M * g.N * 4 > g.part_bytes) continue;
+      if (mode == MODE_FOLD && i != 1) continue;
+      const int steps = ((mode == MODE_SPLIT ? (g.K / 32 + P - 1) / P : g.K / 32) + 1) / 2;
+      double t = WIDE_LAUNCH;
+      for (long left = mode == MODE_SPLIT ? tiles * P : tiles; left > 0; left -= resident)
+        t += w.round + steps * (left >= resident || left > cus ? w.full : w.alone);
+      if (mode == MODE_SPLIT)
+        t += WIDE_SPLIT + (P + 2.0) * g.M * (double)g.N * 4.0 / WIDE_BYTES;
+      if (best.shape < 0 || t < tb) {
+        tb = t;
+        best = WidePick{i, mode};
+      }
+    }
+  }
+  return best;
+}
+
+template <int EPI, int MODE, int RI, int C0, int C1>
+static void launch_wide(const GemmArgs& g, int P, hipStream_t st) {
+  const int MB = (g.M + 64 * RI - 1) / (64 * RI);
+  const int NB = (g.N / 16 + 4 * (C0 + C1) - 1) / (4 * (C0 + C1));
+  const dim3 grid((unsigned)MB * NB * (MODE == MODE_SPLIT ? P : 1));
+  // outputs and residuals of any float alignment (callers' logits and rows)
+  const int vec = (((uintptr_t)g.out | (uintptr_t)g.res) & 15) == 0 && g.ldo % 4 == 0 &&
+                  g.ldres % 4 == 0;
+  KS_LAUNCH((k_gemm_wide<EPI, MODE, RI, C0, C1>), grid, dim3(512), 0, st, g.M, g.N, g.K,
+            (const bf16_t*)g.A.hi, (const bf16_t*)g.W, g.out, g.ldo, g.res, g.ldres,
+            (bf16_t*)g.act_out.hi, g.act_out.kt, MB, NB, P, vec, g.part);
+}
+
+template <int EPI>
+static void launch_epi(const GemmArgs& g, hipStream_t st) {
+  const int P = gemm_parts(g);
+  const WidePick w = wide_pick(g, P);
+  if constexpr (EPI != EPI_SWIGLU) {
+    if (w.mode == MODE_FOLD) return launch_wide<EPI, MODE_FOLD, 2, 2, 2>(g, P, st);
+    if (w.mode == MODE_SPLIT) {
+      switch (w.shape) {
+        case 0: launch_wide<EPI, MODE_SPLIT, 2, 1, 1>(g, P, st); break;
+        case 1: launch_wide<EPI, MODE_SPLIT, 2, 2, 2>(g, P, st); break;
+        case 2: launch_wide<EPI, MODE_SPLIT, 3, 2, 2>(g, P, st); break;
+        default: launch_wide<EPI, MODE_SPLIT, 4, 2, 2>(g, P, st); break;
+      }
+      const size_t n4 = (size_t)g.M * (g.N / 4);
+      KS_LAUNCH(k_splitk_reduce<EPI>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, g.M,
+                g.N, P, g.part, g.out, g.ldo, g.res, g.ldres);
+      return;
+    }
+  }
+  switch (w.shape) {
+    case 0: launch_wide<EPI, MODE_ONE, 2, 1, 1>(g, P, st); break;
+    case 1: launch_wide<EPI, MODE_ONE, 2, 2, 2>(g, P, st); break;
+    case 2: launch_wide<EPI, MODE_ONE, 3, 2, 2>(g, P, st); break;
+    default: launch_wide<EPI, MODE_ONE, 4, 2, 2>(g, P, st); break;
   }
 }
 
-// Workgroup tile 128 x 256 (8 waves of 64 x 64), 3 stages: measured on MI355X
-// at the selection shapes (400..1225 rows of the Llama-8B products) against
-// 128 x 128 / 4 waves (up to 1.3x slower: it moves 33% more operand bytes per
-// flop through the CU's load path), 256 x 128, 256 x 256, 64 x 128 wave tiles
-// and 2..5 stages.
-#ifndef KS_TILED_WM
-#define KS_TILED_WM 4
-#endif
-#ifndef KS_TILED_WN
-#define KS_TILED_WN 4
-#endif
-#ifndef KS_TILED_ST
-#define KS_TILED_ST 3
-#endif
-#ifndef KS_TILED_NWN
-#define KS_TILED_NWN 4
-#endif
-#ifndef KS_TILED_NWM
-#define KS_TILED_NWM 2
-#endif
 void gemm_bf16_tiled(const GemmArgs& g, hipStream_t st) {
-  launch_tiled<KS_TILED_ST, KS_TILED_WM, KS_TILED_WN, KS_TILED_NWM, KS_TILED_NWN>(g, st);
+  if (g.epi == EPI_SWIGLU) launch_epi<EPI_SWIGLU>(g, st);
+  else if (g.epi == EPI_RESID) launch_epi<EPI_RESID>(g, st);
+  else launch_epi<EPI_STORE>(g, st);
 }
 
 // --------------------------------------------------------------------- f32

@@ -70,11 +70,21 @@ enum Epi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 
 // Activations feeding a matrix product.  bf16 models: two bf16 planes with
 // a = hi + lo (lo = bf16(a - hi)); float32 models: one float plane in hi.
+// Batched rows of bf16 models (kt > 0): one bf16 plane in the operand tiles of
+// the matrix instructions, as the weights are: 16 rows x 32 columns per 1 KiB
+// tile, kt tiles per 16 rows (see act_off), so a product stages both operands
+// with loads of whole contiguous tiles.  Rows are padded to a multiple of 16.
 struct Act {
   void* hi;
   void* lo;
-  int ld;  // elements per row
+  int ld;      // elements per row (kt = 0)
+  int kt = 0;  // operand tiles per 16 rows: columns / 32
 };
+// element offset of row m, column c in operand tiles
+__host__ __device__ inline size_t act_off(int m, int c, int kt) {
+  return ((size_t)(m >> 4) * kt + (c >> 5)) * 512 + ((m & 15) + 16 * ((c & 31) >> 3)) * 8 +
+         (c & 7);
+}
 
 // ----------------------------------------------------------- kernel launchers
 // GEMM: y[m][n] = sum_k A[m][k] W[n][k] for m < M, n < N (N = rows of W).
@@ -119,12 +129,14 @@ struct GemmArgs {
   Act next_act{};
   float* next_ssq = nullptr;
   QkvEpi qe{};
-  // tiled path: float32 split-K partial buffer (optional)
+  // batched path: float32 split-K partial buffer (optional) and the rows that
+  // set the parts of the K sum (0: M; a pass over several chunks names one)
   float* part = nullptr;
   size_t part_bytes = 0;
+  int part_rows = 0;
 };
 void gemm_bf16_skinny(const GemmArgs& g, hipStream_t st);  // M <= 16
-void gemm_bf16_tiled(const GemmArgs& g, hipStream_t st);   // any M, A.hi only
+void gemm_bf16_tiled(const GemmArgs& g, hipStream_t st);   // any M, A and act_out in tiles
 void gemm_f32(const GemmArgs& g, hipStream_t st);          // any M
 
 void pack_matrix_bf16(const bf16_t* src, bf16_t* dst, int N, int K, hipStream_t st);
@@ -155,8 +167,8 @@ struct PosFill {
 void act_prep(const float* xin, int ldx, const void* E, int dtype, const int32_t* tok, int M,
               int d, float* xout, const float* gain, Act act, float* ssq, hipStream_t st,
               PosFill pf = PosFill{});
-// act = bf16 split (or f32 copy) of rmsnorm(x) * g ; g == nullptr means no norm (plain
-// conversion).
+// act = bf16 split (operand tiles: one bf16 plane; f32: copy) of rmsnorm(x) * g ;
+// g == nullptr means no norm (plain conversion).
 void norm_act(const float* x, int ldx, const float* g, float eps, int M, int d, int dtype,
               Act act, hipStream_t st);
 // q/k normalisation (optional), RoPE, store of k/v.

@@ -117,7 +117,7 @@ void act_prep(const float* xin, int ldx, const void* E, int dtype, const int32_t
 // partials, wave butterfly, then the 4 wave sums added in order.
 __global__ __launch_bounds__(256) void k_norm_act(const float* __restrict__ x, int ldx,
                                                   const float* __restrict__ g, float eps, int d,
-                                                  int bf, void* ahi, void* alo, int lda) {
+                                                  int bf, void* ahi, void* alo, int lda, int kt) {
   __shared__ float red[4];
   const int m = blockIdx.x;
   const float* xr = x + (size_t)m * ldx;
@@ -151,6 +151,12 @@ __global__ __launch_bounds__(256) void k_norm_act(const float* __restrict__ x, i
       const float4 gg = *(const float4*)(g + c);
       a[0] *= scale * gg.x; a[1] *= scale * gg.y; a[2] *= scale * gg.z; a[3] *= scale * gg.w;
     }
+    if (kt) {  // operand tiles, one plane
+      *(uint2*)((bf16_t*)ahi + act_off(m, c, kt)) =
+          make_uint2((uint32_t)f2bf(a[0]) | ((uint32_t)f2bf(a[1]) << 16),
+                     (uint32_t)f2bf(a[2]) | ((uint32_t)f2bf(a[3]) << 16));
+      return;
+    }
     const size_t off = (size_t)m * lda + c;
     if (bf) {
       uint32_t h[2], l[2];
@@ -178,7 +184,7 @@ void norm_act(const float* x, int ldx, const float* g, float eps, int M, int d, 
               Act act, hipStream_t st) {
   if (M <= 0) return;
   KS_LAUNCH(k_norm_act, dim3(M), dim3(256), 0, st, x, ldx, g, eps, d,
-            dtype == KS_BF16 ? 1 : 0, act.hi, act.lo, act.ld);
+            dtype == KS_BF16 ? 1 : 0, act.hi, act.lo, act.ld, act.kt);
 }
 
 // ------------------------------------------------------- q/k norm, RoPE, KV

@@ -1,0 +1,75 @@
+"""The batched products (k_gemm_wide) at the edges of their tiles, k steps and K
+parts: a one-layer bf16 decoder whose widths leave remainders everywhere
+(d = 4128: 129 k tiles, so steps, parts and folds end in half steps; ffn = 2880;
+vocab = 16048: 1003 column tiles).  By row count the LM head (STORE) takes 128 x
+128 tiles in 8 parts, 192 x 256 tiles in 4 and 128 x 256 tiles unsplit and with
+3 folded parts; the other products take the remaining shapes.  Sampled rows
+against the float64 oracle at the bf16 tolerance of the other tests (2e-2:
+activations are rounded to bf16 once per product, 2^-9 relative each)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import model as M
+from tests.gpu_helpers import check_rows, fill_layer, rel_err
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+TOL = 2e-2
+CFG = dataclasses.replace(W.config("small_bf16"), name="edges_bf16", L=1, d=4128, hq=2, hkv=1,
+                          ffn=2880, vocab=16048)
+ROWS = [17, 130, 300, 520, 700]
+
+
+@pytest.fixture(scope="module")
+def edges():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd.engine import DeviceModel
+    print("\n[setup] edges_bf16", flush=True)
+    w = W.generate_weights(CFG, seed=0)
+    dm = DeviceModel(CFG, n_max=320, gamma_max=4, m_rounds=5, cap_max=64,
+                     prefill_chunk=64).upload_all(w)
+    yield dm, M.Model(CFG, w)
+    dm.close()
+
+
+def _sample(R):
+    return sorted({0, 15, 16, 127, 128, 191, 192, 255, 256, R // 2, R - 2, R - 1} & set(range(R)))
+
+
+@pytest.mark.parametrize("R", ROWS)
+def test_sublayers(edges, R):
+    dm, model = edges
+    n = 90
+    cache = fill_layer(CFG, dm, 0, n, 320)
+    x = W.synthetic_rows(R, CFG.d, seed=4, std=0.5, index=800 + R)
+    pos = (np.arange(R) % n).astype(np.int32)
+    s = _sample(R)
+    for i in (1, 2):
+        out = torch.empty(R, CFG.d, device="cuda")
+        dm.sublayer_apply(i, torch.from_numpy(x).cuda(), pos, mode=1, out=out)
+        got = out.cpu().numpy()
+        ref = M.sublayer(model, i, x[s].astype(np.float64), pos[s], cache, mode="own")
+        check_rows(got[s], x[s], ref, TOL, ("edges", R, i))
+        x = got
+
+
+@pytest.mark.parametrize("R", ROWS)
+def test_head(edges, R):
+    dm, model = edges
+    x = torch.from_numpy(W.synthetic_rows(R, CFG.d, seed=4, std=0.5, index=900 + R)).cuda()
+    logits, am, top1 = dm.head_rows(x)
+    s = _sample(R)
+    lg0, _, _ = M.head(model, x.cpu().numpy()[s].astype(np.float64))
+    assert rel_err(logits.cpu().numpy()[s], lg0) < TOL
+    assert torch.equal(am.long(), logits.argmax(-1))
+    # logits at an address that is a multiple of 4 bytes only: the same bits
+    from paper_2602_20217_amd import _lib as K
+    flat = torch.full((R * CFG.vocab + 8,), 7.0, device="cuda")
+    K.ks_head_rows(dm.ctx, x.data_ptr(), R, flat.data_ptr() + 4, am.data_ptr(), top1.data_ptr())
+    assert torch.equal(flat[1:1 + R * CFG.vocab].view(R, -1), logits)
+    assert bool((flat[0] == 7) & (flat[1 + R * CFG.vocab:] == 7).all())

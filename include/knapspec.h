@@ -67,7 +67,8 @@ typedef struct ks_limits {
   int gamma_max;      /* longest draft; verify runs gamma+1 rows (<= 15) */
   int m_rounds;       /* history keeps the last m rounds (paper: 5) */
   int cap_max;        /* largest knapsack capacity C accepted by the selection */
-  int prefill_chunk;  /* rows per prefill pass (multiple of 16) */
+  int prefill_chunk;  /* rows per prefill chunk (multiple of 16): sets how the products
+                         sum; a pass runs as many whole chunks as the workspace holds */
 } ks_limits;
 
 /*

@@ -7,8 +7,8 @@
 //      cache size, so a verify row and the decode step at the same position
 //      compute the same bits and greedy speculative output equals greedy AR
 //      output.
-//  prefill (512-row chunks) and selection DP (budgets x history rows): tiled
-//      MFMA products with split-K, batched attention.
+//  prefill (passes of whole chunks) and selection DP (budgets x history rows):
+//      tiled MFMA products, batched attention.
 //  selection (Sections 3.3-3.5): stage 1 runs on the device one sublayer at a
 //      time over the reachable budgets; per-row cosines (float64) of both
 //      candidates, the decisions of Eq. dp_main with the tau and C/2 pruning,
@@ -58,6 +58,11 @@ constexpr int PB = 512;        // rows per batched head pass
 // split partials of a pass would exceed PA_PART_BYTES
 constexpr int PA_MAX = 1280;
 constexpr size_t PA_PART_BYTES = (size_t)1 << 30;
+// rows of a prefill pass: 16 row tiles of 256, i.e. whole rounds of 256
+// workgroups in the O, gate/up and down products of the 8B shapes.  8192 tokens
+// in chunks of 512 through two layers: 12.5 -> 10.0 ms; 1237 in chunks of 256:
+// 2.59 -> 1.86 ms (one pass against one chunk at a time).
+constexpr int PASS_MAX = 4096;
 // float32 split-K partials of the batched products (prefill chunks, selection)
 constexpr size_t GPART_BYTES = (size_t)128 << 20;
 // decode/verify splits: 64-position tiles per split, by the model's cache size
@@ -95,7 +100,7 @@ struct Layout {
   size_t tok, pos, len, stage, hist, xh, g0, g1, ge, dpos, dlen, sig, ptrs, ssq, gpart;
   size_t dpc, dpn, dpmean, dpidx, dpbits, dpreach, dpse, dpss;
   size_t vws, tab_ids, tab_pr, tab_cnt, sres, total;
-  int FR, RING, cells, DR, XR, LR, nqkv, a2w, part_rows, PA;
+  int FR, PR, RING, cells, DR, XR, LR, nqkv, a2w, part_rows, PA;
   size_t part_elems;
 };
 
@@ -107,6 +112,9 @@ Layout make_layout(const ks_model_desc& d, const ks_limits& lim) {
   y.cells = lim.cap_max + 1;
   y.DR = y.cells * y.RING;
   y.XR = std::max(y.FR, y.DR);
+  // prefill pass: as many whole chunks as the row buffers hold anyway (the
+  // selection's candidates size them), up to PASS_MAX rows
+  y.PR = std::max(lim.prefill_chunk, std::min(y.XR, PASS_MAX) / lim.prefill_chunk * lim.prefill_chunk);
   const size_t AR = align16(y.XR);  // activation rows: whole operand tiles
   y.LR = std::max(gam1, PB);
   y.nqkv = (d.hq + 2 * d.hkv) * d.hd;
@@ -137,7 +145,7 @@ Layout make_layout(const ks_model_desc& d, const ks_limits& lim) {
   y.logits = take((size_t)y.LR * d.vocab * 4);
   y.am = take((size_t)(y.XR + y.RING + 64) * 4);
   y.top1 = take((size_t)(y.XR + 64) * 4);
-  y.tok = take((size_t)(y.FR + 64) * 4);
+  y.tok = take((size_t)(std::max(y.FR, y.PR) + 64) * 4);
   y.pos = take((size_t)y.XR * 4);
   y.len = take((size_t)y.XR * 4);
   y.stage = take((size_t)(2 * d.L + 1) * gam1 * d.d * 4);
@@ -273,7 +281,7 @@ void prof_end(ks_ctx* c, int i) {
 // (the embedding, a residual epilogue, or act_prep for rows handed in).
 bool skinny(const ks_ctx* c, int M, bool batched) { return c->bf() && !batched && M <= 16; }
 
-void run_gemm(ks_ctx* c, GemmArgs& g, bool batched) {
+void run_gemm(ks_ctx* c, GemmArgs& g, bool batched, int part_rows = 0) {
   if (!c->bf()) {
     gemm_f32(g, c->st);
   } else if (skinny(c, g.M, batched)) {
@@ -281,14 +289,15 @@ void run_gemm(ks_ctx* c, GemmArgs& g, bool batched) {
   } else {
     g.part = c->at<float>(c->y.gpart);
     g.part_bytes = GPART_BYTES;
+    g.part_rows = part_rows;
     gemm_bf16_tiled(g, c->st);
   }
 }
 
 void gemm(ks_ctx* c, int M, int N, int K, Act A, const void* W, int epi, float* out, int ldo,
-          const float* res, int ldres, Act aout, bool batched) {
+          const float* res, int ldres, Act aout, bool batched, int part_rows = 0) {
   GemmArgs g{M, N, K, A, W, epi, out, ldo, res, ldres, aout};
-  run_gemm(c, g, batched);
+  run_gemm(c, g, batched, part_rows);
 }
 
 // norm gain feeding sublayer i (1..2L); i = 2L + 1 is the final norm
@@ -318,7 +327,7 @@ GemmArgs normed(ks_ctx* c, int M, int N, const void* W, int epi, float* out, int
 // residual product; on the skinny path with next_gain it also writes the
 // planes and tile sums of its output for the next normed product
 void resid_gemm(ks_ctx* c, int R, int K, Act A, const void* W, float* xout, const float* xin,
-                bool batched, const float* next_gain) {
+                bool batched, const float* next_gain, int part_rows) {
   const ks_model_desc& d = c->md;
   GemmArgs g{R, d.d, K, A, W, EPI_RESID, xout, d.d, xin, d.d, Act{}};
   if (skinny(c, R, batched) && next_gain) {
@@ -326,13 +335,15 @@ void resid_gemm(ks_ctx* c, int R, int K, Act A, const void* W, float* xout, cons
     g.next_act = c->act1();
     g.next_ssq = c->at<float>(c->y.ssq);
   }
-  run_gemm(c, g, batched);
+  run_gemm(c, g, batched, part_rows);
 }
 
 // Attention sublayer of layer l on R rows: x_out = x_in + Wo attn(...).
 // mode 0: keys/values stored at pos; mode 1: own key/value (selection DP).
+// part_rows: rows that set the parts of the batched products' K sums (0: R).
 void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int32_t* pos,
-               const int32_t* len, int max_len, int mode, bool batched, const float* next_gain) {
+               const int32_t* len, int max_len, int mode, bool batched, const float* next_gain,
+               int part_rows) {
   const ks_model_desc& d = c->md;
   const bool sk = skinny(c, R, batched);
   const Act a1 = sk ? c->act1() : c->bact1(), a2 = sk ? c->act2() : c->bact2(d.hq * d.hd);
@@ -360,7 +371,7 @@ void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int
          norm_act(xin, d.d, c->attn_norm[l], d.eps, R, d.d, d.dtype, a1, c->st));
     PROF(c, KS_KC_GEMM_QKV,
          gemm(c, R, c->y.nqkv, d.d, a1, c->wqkv[l], EPI_STORE, qkv, c->y.nqkv, nullptr, 0,
-              Act{}, batched));
+              Act{}, batched, part_rows));
     QkvPostArgs qp{R, d.hq, d.hkv, d.hd, d.n_max, d.dtype, d.qk_norm, d.eps, qkv, rope,
                    c->q_norm[l], c->k_norm[l], pos, q, c->kc(l), c->vc(l), kvs, mode,
                    c->bf() ? 1 : 0};
@@ -384,11 +395,12 @@ void attn_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, const int
          attn_combine(aa, mode == 1 ? kvs + (size_t)r0 * 2 * d.hkv * d.hd : nullptr, out2,
                       c->st));
   }
-  PROF(c, KS_KC_GEMM_O, resid_gemm(c, R, d.hq * d.hd, a2, c->wo[l], xout, xin, batched, next_gain));
+  PROF(c, KS_KC_GEMM_O,
+       resid_gemm(c, R, d.hq * d.hd, a2, c->wo[l], xout, xin, batched, next_gain, part_rows));
 }
 
 void mlp_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, bool batched,
-              const float* next_gain) {
+              const float* next_gain, int part_rows) {
   const ks_model_desc& d = c->md;
   const bool sk = skinny(c, R, batched);
   const Act a1 = sk ? c->act1() : c->bact1(), a2 = sk ? c->act2() : c->bact2(d.ffn);
@@ -403,7 +415,8 @@ void mlp_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, bool batch
          gemm(c, R, 2 * d.ffn, d.d, a1, c->wgu[l], EPI_SWIGLU, nullptr, 0, nullptr, 0, a2,
               batched));
   }
-  PROF(c, KS_KC_GEMM_DOWN, resid_gemm(c, R, d.ffn, a2, c->wdown[l], xout, xin, batched, next_gain));
+  PROF(c, KS_KC_GEMM_DOWN,
+       resid_gemm(c, R, d.ffn, a2, c->wdown[l], xout, xin, batched, next_gain, part_rows));
 }
 
 // Sublayer i on R rows.  Skinny path: the planes of x_in for sublayer i's norm
@@ -411,10 +424,12 @@ void mlp_rows(ks_ctx* c, int l, const float* xin, float* xout, int R, bool batch
 // product).
 void sublayer_rows(ks_ctx* c, int i, const float* xin, float* xout, int R, const int32_t* pos,
                    const int32_t* len, int max_len, int mode, bool batched,
-                   const float* next_gain = nullptr) {
+                   const float* next_gain = nullptr, int part_rows = 0) {
   const int l = (i - 1) / 2;
-  if (i % 2 == 1) attn_rows(c, l, xin, xout, R, pos, len, max_len, mode, batched, next_gain);
-  else mlp_rows(c, l, xin, xout, R, batched, next_gain);
+  if (i % 2 == 1)
+    attn_rows(c, l, xin, xout, R, pos, len, max_len, mode, batched, next_gain, part_rows);
+  else
+    mlp_rows(c, l, xin, xout, R, batched, next_gain, part_rows);
 }
 
 // final norm + LM head + argmax for R rows (chunked by the logits buffer);
@@ -726,21 +741,22 @@ ks_status ks_prefill(ks_ctx* c, const int32_t* tokens, int n, int32_t* out_first
   int32_t* pos = c->at<int32_t>(c->y.pos);
   int32_t* len = c->at<int32_t>(c->y.len);
   int32_t* am = c->at<int32_t>(c->y.am);
-  for (int c0 = 0; c0 < n; c0 += FR) {
-    const int R = std::min(FR, n - c0);
+  // Passes of whole chunks, then the ragged chunk.  The products' K parts are
+  // those of a chunk, so a pass gives the bits of one chunk at a time (float32
+  // models: rows do not depend on how many there are either).
+  for (int c0 = 0, R = 0; c0 < n; c0 += R) {
+    const int whole = (n - c0) / FR * FR;
+    R = whole ? std::min(whole, c->y.PR) : n - c0;
     HIPCHK(hipMemcpyAsync(tok, tokens + c0, R * 4, hipMemcpyHostToDevice, c->st));
     fill_pos(pos, len, c0, R, R, 1, c->st);
     embed_rows(c->embed, d.dtype, tok, R, d.d, x, d.d, c->st);
-    const int h0 = std::max(c0, n - r0);  // first history row in this chunk
+    const int h0 = std::max(c0, n - r0);  // first history row in this pass
     for (int i = 0; i <= 2 * d.L; ++i) {
-      if (i > 0) sublayer_rows(c, i, x, x, R, pos, len, c0 + R, 0, true);
-      for (int p = h0; p < c0 + R;) {
-        const int slot = p % c->y.RING;
-        const int run = std::min(c0 + R - p, c->y.RING - slot);
-        HIPCHK(hipMemcpyAsync(c->hist_row(i, slot), x + (size_t)(p - c0) * d.d,
-                              (size_t)run * d.d * 4, hipMemcpyDeviceToDevice, c->st));
-        p += run;
-      }
+      if (i > 0)
+        sublayer_rows(c, i, x, x, R, pos, len, c0 + R, 0, true, nullptr, std::min(R, FR));
+      if (h0 < c0 + R)
+        ring_copy(x + (size_t)(h0 - c0) * d.d, c->hist_row(i, 0), 0, 1, c0 + R - h0, c->y.RING,
+                  h0, d.d, true, c->st);
     }
     if (c0 + R == n) {
       const SampleSpec ss = c->spec(0, nullptr, am, n, 2);

@@ -73,3 +73,25 @@ def test_head(edges, R):
     K.ks_head_rows(dm.ctx, x.data_ptr(), R, flat.data_ptr() + 4, am.data_ptr(), top1.data_ptr())
     assert torch.equal(flat[1:1 + R * CFG.vocab].view(R, -1), logits)
     assert bool((flat[0] == 7) & (flat[1 + R * CFG.vocab:] == 7).all())
+
+
+def test_prefill_passes_keep_the_bits_of_single_chunks(edges):
+    """A prefill pass holds as many whole chunks as the row buffers do: 1100
+    tokens in chunks of 64 run as one pass of 1088 rows (down projection: 8 parts
+    folded in one workgroup, several ending between the k tiles of a step) and a
+    ragged chunk; limits that leave room for one chunk run them one by one.  Same
+    caches, same token."""
+    from paper_2602_20217_amd.engine import DeviceModel
+    n = 1100
+    cfg = dataclasses.replace(CFG, L=2)
+    w = W.generate_weights(cfg, seed=0)
+    prompt = W.prompt_ids(cfg.vocab, n)
+    runs = []
+    for lim in (dict(gamma_max=4, m_rounds=5, cap_max=64), dict(gamma_max=0, m_rounds=1, cap_max=1)):
+        dm = DeviceModel(cfg, n_max=n + 20, prefill_chunk=64, **lim).upload_all(w)
+        first = dm.prefill(prompt)
+        runs.append((first, [t[:, :n].clone() for l in range(2) for t in dm.kv_layer(l)]))
+        dm.close()
+    assert runs[0][0] == runs[1][0]
+    for a, b in zip(runs[0][1], runs[1][1]):
+        assert torch.equal(a, b)

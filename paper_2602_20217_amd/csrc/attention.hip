@@ -26,6 +26,7 @@
 #include "ks_internal.h"
 
 #include <cfloat>
+#include <type_traits>
 
 namespace ks {
 
@@ -44,16 +45,6 @@ __device__ inline SplitId split_id(int xmap) {
   if (xmap) return SplitId{(int)(blockIdx.x >> 3), (int)(blockIdx.x & 7)};
   return SplitId{(int)blockIdx.x, (int)blockIdx.y};
 }
-#ifndef KS_BAT_NW
-#define KS_BAT_NW 8  // waves (16 query vectors each) per batched workgroup
-#endif
-#ifndef KS_BAT_ST
-#define KS_BAT_ST 2  // LDS ring stages of the batched kernel
-#endif
-#ifndef KS_BAT_CB
-#define KS_BAT_CB 1  // 16-vector query blocks per wave of the batched kernel
-#endif
-
 // s_waitcnt immediate: vmcnt = n, expcnt and lgkmcnt not waited for
 __device__ constexpr int vmcnt_imm_a(int n) {
   return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14);
@@ -837,76 +828,131 @@ __global__ __launch_bounds__(64 * NW) void k_attn_stream(
   }
 }
 
+// max / sum of the two lanes whose index differs in bit 4 or bit 5 (both lanes
+// get it), on the vector ALU instead of the LDS permute unit
+__device__ inline float max_x16(float v) {
+  const auto r =
+      __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float max_x32(float v) {
+  const auto r =
+      __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float sum_x16(float v) {
+  const auto r =
+      __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float sum_x32(float v) {
+  const auto r =
+      __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// 16 bytes per lane from base + off straight into LDS at byte `lds` + 16 lane.
+// Written out so that the compiler, which cannot tell the ring's stages apart,
+// puts no wait for it before LDS reads; the kernel counts its own waits.  (No
+// register is written, so none can be overwritten late.)
+__device__ inline void load_lds16(const void* base, uint32_t off, uint32_t lds) {
+  __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                   :
+                   : "v"(off), "s"(base), "s"(lds)
+                   : "memory", "m0");
+}
+
 // Batched rows (prefill chunks, selection candidates), bf16 caches, head dim
 // 128.  Query vectors of one kv head are ordered qi = row * G + g; wave w of a
-// workgroup owns 16 CB consecutive ones in CB column blocks (each key fragment
-// and each transposed value read from LDS feeds CB matrix instructions; one
-// block measured fastest, as two need 240 VGPRs).  The workgroup walks the
-// 64-key tiles of
-// its split through a ring of ST LDS stages filled by direct global-to-LDS
-// loads ST - 1 tiles ahead (one barrier per tile, no staging registers); rows
-// are stored with 16-byte chunk c of row r at slot c ^ (r % 16).  Per tile and
-// wave: S^T = K Q^T (keys as rows, queries as hi + lo bf16 columns), an online
-// softmax per query column (two cross-lane steps per statistic), then O += P V
-// with the probabilities (bf16) taken from the score registers and the value
-// operand from transposing LDS reads in the same key order.  The softmax is
-// kept light, as the vector ALU and not the matrix unit bounds this kernel:
-// scores arrive in base-2 units (queries pre-scaled), keys are masked only in
-// tiles that reach past the shortest column of the wave, and the rescale of
-// the running output is skipped when no column's max moved (its factor would
-// be exactly 1).  Tile rows at or past max_len repeat row max_len - 1 (finite;
-// their probability is 0).  Partials use the layout of the split kernels
-// (max in natural-log units).
-template <int NW, int ST, int CB>
-__global__ __launch_bounds__(NW * 64) void k_attn_bat(int M, int hq, int hkv, int n_max,
-                                                      const float* __restrict__ q,
-                                                      const bf16_t* __restrict__ kc,
-                                                      const bf16_t* __restrict__ vc,
-                                                      const int32_t* __restrict__ len,
-                                                      int max_len, int span,
-                                                      float* __restrict__ part, int nsplit) {
-  constexpr int HD = 128;
-  constexpr int PPW = 32 / NW;  // 1 KiB pieces per wave per tile
-  constexpr int QW = 16 * CB;   // query vectors per wave
-  __shared__ __align__(16) uint4 KV[ST][2 * TILE * 16];
-  const int split = blockIdx.x, kvh = blockIdx.y;
-  const int G = hq / hkv;
-  const int NQ = M * G;
+// workgroup of four owns 16 CB consecutive ones in CB column blocks, so each key
+// fragment and each transposed value read from LDS feeds CB matrix instructions.
+// A workgroup walks the 64-key tiles of one split of `span` positions through a
+// two-stage LDS ring filled by direct global-to-LDS loads one tile ahead (one
+// barrier per tile).  Per tile and wave:
+// S^T = K Q^T (keys as rows, queries as hi + lo bf16 columns), an online softmax
+// per query column (two cross-lane steps per statistic), then O^T += V^T P^T with
+// the probabilities (bf16) taken from the score registers and the value operand
+// from transposing LDS reads in the same key order; a lane's scores, statistics
+// and outputs all belong to one column, so the rescale needs no lane exchange.
+// Scores arrive in base-2 units (queries pre-scaled), keys are masked only in
+// tiles that reach past the shortest column of the wave, and the rescale is
+// skipped when no column's max moved (its factor would be exactly 1).
+//
+// What bounds it: the matrix unit (48 instructions of 16 clocks per wave, tile
+// and block) and the vector ALU (about 130 instructions, 16 of them exponentials)
+// are each busy about half of the time; two workgroups per CU, which share no
+// barrier, overlap the one with the other and one workgroup's start with the
+// other's arithmetic.  1295 rows of 32 heads over 32768 positions: 1180 -> 1026
+// us; 512 rows over 8192: 117 -> 104; with one block per wave 213 rows over 1237:
+// 35 -> 21, 25 rows over 8192: 35 -> 21 (before: eight waves of one block, each
+// key fragment waited for where it was used, output rows rescaled across lanes).
+// Slower: 8 waves in two groups that alternate segments of matrix and vector
+// work behind barriers (1234 us), scores of the next tile and values of the last
+// one interleaved with the softmax in one wave (1263 us), merging the splits of a
+// row inside the workgroup (1160 us; its 1312 workgroups leave a ragged round).
+//
+// Partials use the layout of the split kernels (max in natural-log units).  Tile
+// rows at or past max_len repeat row max_len - 1 (finite; their probability is 0).
+template <int CB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bat(
+    int M, int hq, int hkv, int n_max, const float* __restrict__ q,
+    const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
+    const int32_t* __restrict__ len, int max_len, int span, float* __restrict__ part,
+    int nsplit) {
+  constexpr int HD = 128, NW = 4, QW = 16 * CB, QB = NW * QW;
+  constexpr int SB = TILE * HD * 2;  // bytes of a key or value tile
+  constexpr int PPW = 16 / NW;       // 1 KiB pieces of a tile per wave
+  __shared__ __align__(16) char KV[4 * SB];  // keys 0, values 0, keys 1, values 1
+  // one-dimensional grid: kv head, query block, split.  Workgroups are dealt
+  // round-robin to the 8 XCDs, so with 8 kv heads the query blocks of a head
+  // share its key and value tiles in one L2
+  const int G = hq / hkv, NQ = M * G, nz = (NQ + QB - 1) / QB;
+  const int kvh = (int)(blockIdx.x % hkv), rest = (int)(blockIdx.x / hkv);
+  const int z = rest % nz, split = rest / nz;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, g = lane >> 4;
+  // longest row of the workgroup: no tile past it is loaded
+  const int q0 = z * QB;
+  const int rA = q0 / G, rB = min(M - 1, (q0 + QB - 1) / G);
+  int Lmax = 0;
+  for (int r = rA + lane; r <= rB; r += 64) Lmax = max(Lmax, len[r]);
+#pragma unroll
+  for (int o_ = 32; o_ >= 1; o_ >>= 1) Lmax = max(Lmax, __shfl_xor(Lmax, o_));
   const int start = split * span;
-  const int end = min(max_len, start + span);
-  const int ntile = (end - start + TILE - 1) / TILE;  // >= 1: the grid covers max_len
+  const int end = __builtin_amdgcn_readfirstlane(min(min(Lmax, max_len), start + span));
+  if (start >= end) return;
 
-  // piece i (1 KiB) of a tile: rows 4 (i % 16) .. + 3 of K (i < 16) or V
-  const bf16_t* kb = kc + (size_t)kvh * n_max * HD;
-  const bf16_t* vb = vc + (size_t)kvh * n_max * HD;
-  auto issue = [&](int tile, int buf) {
-    const int t0 = start + tile * TILE;
+  // piece p (1 KiB) of a tile: rows 4 p .. + 3; wave w moves pieces PPW w ..
+  // 16-byte chunk c of row r lies at slot c ^ (r % 16) of a key row (16 rows of
+  // one chunk on all banks) and c ^ 2 (r % 8) of a value row (8 rows of one
+  // 32-byte piece on all banks, as the transposing reads take them)
+  const char* kb = (const char*)(kc + (size_t)kvh * n_max * HD);
+  const char* vb = (const char*)(vc + (size_t)kvh * n_max * HD);
+  const int pr = 4 * PPW * w + (lane >> 4);  // row of piece PPW w; + 4 per piece
+  uint32_t ck[PPW];
 #pragma unroll
-    for (int u = 0; u < PPW; ++u) {
-      const int i = w * PPW + u;
-      const int rr = 4 * (i & 15) + (lane >> 4);
-      const int row = min(t0 + rr, max_len - 1);
-      const bf16_t* src =
-          (i < 16 ? kb : vb) + (size_t)row * HD + (((lane & 15) ^ (rr & 15)) << 3);
-      __builtin_amdgcn_global_load_lds((const void*)src,
-                                       (__attribute__((address_space(3))) void*)&KV[buf][i * 64],
-                                       16, 0, 0);
-    }
+  for (int u = 0; u < PPW; ++u) ck[u] = ((lane & 15) ^ ((pr + 4 * u) & 15)) << 4;
+  const uint32_t cv = ((lane & 15) ^ (2 * (pr & 7))) << 4;  // piece u: cv ^ 128 (u % 2)
+  auto issue = [&](int t0, int buf) {
+    const int lastrow = max_len - 1 - t0;
+    const size_t to = (size_t)t0 * (HD * 2);
+    const uint32_t at = 2 * buf * SB + 1024 * PPW * w;
+#pragma unroll
+    for (int u = 0; u < PPW; ++u)
+      load_lds16(kb + to, ((uint32_t)min(pr + 4 * u, lastrow) << 8) + ck[u], at + 1024 * u);
+#pragma unroll
+    for (int u = 0; u < PPW; ++u)
+      load_lds16(vb + to, ((uint32_t)min(pr + 4 * u, lastrow) << 8) + (cv ^ (128 * (u & 1))),
+                 at + SB + 1024 * u);
   };
-#pragma unroll
-  for (int s = 0; s < ST - 1; ++s)
-    if (s < ntile) issue(s, s);
+  issue(start, 0);
 
-  // query column j of block b of this wave: vector qb + 16 b + j.  Queries are
-  // scaled by log2(e) / sqrt(HD), so scores are in base-2 units and the
-  // probabilities are plain powers of two.
+  // query column j of block b of this wave: vector qb + 16 b + j, scaled by
+  // log2(e) / sqrt(HD): scores in base-2 units, probabilities powers of two
   const float qscale = 1.4426950408889634f / sqrtf((float)HD);
-  const int qb = (blockIdx.z * NW + w) * QW;
-  int lim[CB];      // keys of the column in this split
-  int lim_min = end;  // fewest keys over the wave's columns with a query
+  const int qb = q0 + w * QW;
+  int lim[CB];        // keys of the column in this split
+  int lim_min = end;  // fewest over the wave's columns with a query
   bf16x8_d qh[CB][4], ql[CB][4];
 #pragma unroll
   for (int b = 0; b < CB; ++b) {
@@ -933,7 +979,8 @@ __global__ __launch_bounds__(NW * 64) void k_attn_bat(int M, int hq, int hkv, in
   }
 #pragma unroll
   for (int o_ = 32; o_ >= 1; o_ >>= 1) lim_min = min(lim_min, __shfl_xor(lim_min, o_));
-  f32x4_d o[CB][8];
+  lim_min = __builtin_amdgcn_readfirstlane(lim_min);
+  f32x4_d o[CB][8];  // o[b][dt][v]: column j, dim 16 dt + 4 g + v
   float m_run[CB], l_run[CB];
 #pragma unroll
   for (int b = 0; b < CB; ++b) {
@@ -942,83 +989,118 @@ __global__ __launch_bounds__(NW * 64) void k_attn_bat(int M, int hq, int hkv, in
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[b][dt] = f32x4_d{0.f, 0.f, 0.f, 0.f};
   }
-  const int s4 = (lane & 15) >> 2, u4 = lane & 3;
+  // key fragment (kt, ks): row 16 kt + j, chunk 4 ks + g, at koff ^ 64 ks + 4096 kt;
+  // value piece of dims 16 dt .., rows 4 g + s (+ 16 per 4 KiB): at voff ^ 32 dt
+  const uint32_t koff = (uint32_t)(j * 256 + ((g ^ j) << 4));
+  const int vrow = 4 * g + ((lane & 15) >> 2), u4 = lane & 3;
+  const uint32_t voff =
+      (uint32_t)(vrow * 256 + (((u4 >> 1) ^ (2 * (vrow & 7))) << 4) + ((u4 & 1) << 3));
 
-  auto step = [&](int it, int buf) {
-    // tile it has landed once at most ST - 2 later tiles are in flight; the
-    // barrier needs no fence (see k_gemm_tiled)
-    if (it + ST - 2 < ntile) __builtin_amdgcn_s_waitcnt(vmcnt_imm_a(PPW * (ST - 2)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm_a(0));
+  auto step = [&](int t0, auto buf_) {
+
+    constexpr int buf = decltype(buf_)::value;
+    // this wave's loads of the tile have landed; the barrier makes every wave's
+    // visible and frees the other stage (its reads fed matrix instructions)
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm_a(0));
+    __asm__ volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     __asm__ volatile("" ::: "memory");
-    if (it + ST - 1 < ntile) issue(it + ST - 1, (buf + ST - 1) % ST);
-    const uint4* Kt = &KV[buf][0];
-    const char* Vb = (const char*)&KV[buf][TILE * 16];
-    const int t0 = start + it * TILE;
-    // keys past a column's length only in tiles that reach past the shortest
-    // column of the wave (wave-uniform)
-    const bool edge = t0 + TILE > lim_min;
-    // S^T per column block; each key fragment feeds every block
+    if (t0 + TILE < end) issue(t0 + TILE, buf ^ 1);
+    const char* Kt = KV + 2 * buf * SB;
+    const char* Vt = Kt + SB;
+    // scores, keys as rows: sc[b][kt][v] = score(key 16 kt + 4 g + v, column j); the
+    // chains run side by side, the next key fragments are requested ahead
+    bf16x8_d kf[2][4];
+    auto read_k = [&](int ks, int at) {
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+        kf[at][kt] =
+            __builtin_bit_cast(bf16x8_d, *(const uint4*)(Kt + (koff ^ (64 * ks)) + kt * 4096));
+    };
     f32x4_d sc[CB][4];
+    read_k(0, 0);
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks < 3) read_k(ks + 1, (ks + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < CB; ++b) sc[b][kt] = f32x4_d{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int c = 4 * ks + g;
-        const bf16x8_d kf = __builtin_bit_cast(bf16x8_d, Kt[(16 * kt + j) * 16 + (c ^ j)]);
+        for (int b = 0; b < CB; ++b)
+          sc[b][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              kf[ks & 1][kt], qh[b][ks], ks ? sc[b][kt] : f32x4_d{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-        for (int b = 0; b < CB; ++b) {
-          sc[b][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qh[b][ks], sc[b][kt], 0, 0, 0);
-          sc[b][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, ql[b][ks], sc[b][kt], 0, 0, 0);
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+          sc[b][kt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks & 1][kt], ql[b][ks], sc[b][kt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    auto read_v = [&](int p, int at) {  // (k2, dims) = (p / 2, 64 (p % 2) ..)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        bf16x4_d h2[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          h2[h] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+              (__attribute__((address_space(3))) bf16x4_d*)(Vt + (voff ^ (32 * (4 * (p & 1) + d))) +
+                                                           (32 * (p >> 1) + 16 * h) * 256));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          kf[at][d][e] = h2[0][e];
+          kf[at][d][4 + e] = h2[1][e];
         }
       }
-    }
+    };
     bf16x8_d pa[CB][2];
+    float mt[CB], ps[CB];
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
-      if (edge) {
+      if (t0 + TILE > lim_min) {  // keys past a column's length
 #pragma unroll
         for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             if (t0 + 16 * kt + 4 * g + v >= lim[b]) sc[b][kt][v] = -FLT_MAX;
       }
-      float mt = -FLT_MAX;
+      mt[b] = -FLT_MAX;
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) mt = fmaxf(mt, sc[b][kt][v]);
-      mt = fmaxf(mt, __shfl_xor(mt, 16));
-      mt = fmaxf(mt, __shfl_xor(mt, 32));
-      const float m_new = fmaxf(m_run[b], mt);
-      float ps = 0.f;
+        for (int v = 0; v < 4; ++v) mt[b] = fmaxf(mt[b], sc[b][kt][v]);
+    }
 #pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
+    for (int b = 0; b < CB; ++b) mt[b] = fmaxf(m_run[b], max_x32(max_x16(mt[b])));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+    for (int b = 0; b < CB; ++b) ps[b] = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
           // masked scores give 2^(-huge) = 0
-          const float p = __builtin_amdgcn_exp2f(sc[b][kt][v] - m_new);
+          const float p = __builtin_amdgcn_exp2f(sc[b][kt][v] - mt[b]);
           sc[b][kt][v] = p;
-          ps += p;
+          ps[b] += p;
         }
-      ps += __shfl_xor(ps, 16);
-      ps += __shfl_xor(ps, 32);
-      // a column whose max moved rescales its sum and output rows; when no
-      // column of the wave moved the factor is exactly 1 and is skipped
-      if (__ballot(m_new != m_run[b])) {
-        const float alpha = m_run[b] == -FLT_MAX ? 0.f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
+#pragma unroll
+    for (int b = 0; b < CB; ++b) ps[b] = sum_x32(sum_x16(ps[b]));
+    // a column whose max moved rescales its sum and output; when no column of a
+    // block moved the factor is exactly 1 and is skipped
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      if (__ballot(mt[b] != m_run[b])) {
+        const float alpha = m_run[b] == -FLT_MAX ? 0.f : __builtin_amdgcn_exp2f(m_run[b] - mt[b]);
         l_run[b] *= alpha;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float av = __shfl(alpha, 4 * g + v);
+        for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-          for (int dt = 0; dt < 8; ++dt) o[b][dt][v] *= av;
-        }
+          for (int v = 0; v < 4; ++v) o[b][dt][v] *= alpha;
       }
-      l_run[b] += ps;
-      m_run[b] = m_new;
+      l_run[b] += ps[b];
+      m_run[b] = mt[b];
 #pragma unroll
       for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
@@ -1027,59 +1109,37 @@ __global__ __launch_bounds__(NW * 64) void k_attn_bat(int M, int hq, int hkv, in
           pa[b][k2][4 + v] = (__bf16)sc[b][2 * k2 + 1][v];
         }
     }
-    // O += P V; each transposed value operand feeds every block
+    read_v(0, 0);
 #pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
+    for (int p = 0; p < 4; ++p) {
+      if (p < 3) read_v(p + 1, (p + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        bf16x4_d h2[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = 32 * k2 + 16 * h + 4 * g + s4;
-          const int c = 2 * dt + (u4 >> 1);
-          const char* pp = Vb + row * 256 + ((c ^ (row & 15)) << 4) + ((u4 & 1) << 3);
-          h2[h] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-              (__attribute__((address_space(3))) bf16x4_d*)pp);
-        }
-        bf16x8_d vbv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vbv[e] = h2[0][e];
-          vbv[4 + e] = h2[1][e];
-        }
+      for (int d = 0; d < 4; ++d)
 #pragma unroll
         for (int b = 0; b < CB; ++b)
-          o[b][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[b][k2], vbv, o[b][dt], 0, 0, 0);
-      }
+          o[b][4 * (p & 1) + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              kf[p & 1][d], pa[b][p >> 1], o[b][4 * (p & 1) + d], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // the ring position is a constant of each unrolled copy
-  for (int it0 = 0; it0 < ntile; it0 += ST) {
-#pragma unroll
-    for (int u = 0; u < ST; ++u)
-      if (it0 + u < ntile) step(it0 + u, u);
+  for (int t0 = start; t0 < end; t0 += 2 * TILE) {
+    step(t0, std::integral_constant<int, 0>{});
+    if (t0 + TILE < end) step(t0 + TILE, std::integral_constant<int, 1>{});
   }
 
-  // partials: O rows of block b are query columns 16 b + 4 g + v, dims 16 dt + j;
-  // the max goes back to natural-log units
+  // (a partial is 130 floats: 8-byte aligned)
 #pragma unroll
   for (int b = 0; b < CB; ++b) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int qv = qb + 16 * b + 4 * g + v;
-      const int lv = __shfl(lim[b], 4 * g + v);
-      if (qv >= NQ || lv <= start) continue;
-      const int row = qv / G, h = kvh * G + qv % G;
-      float* dst = part + (((size_t)row * hq + h) * nsplit + split) * (HD + 2);
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) dst[16 * dt + j] = o[b][dt][v];
-    }
     const int qi = qb + 16 * b + j;
-    if (g == 0 && qi < NQ && lim[b] > start) {
-      const int row = qi / G, h = kvh * G + qi % G;
-      float* dst = part + (((size_t)row * hq + h) * nsplit + split) * (HD + 2);
-      dst[HD] = m_run[b] * 0.6931471805599453f;
-      dst[HD + 1] = l_run[b];
+    if (qi < NQ && lim[b] > start) {
+      float* dst = part + (((size_t)(qi / G) * hq + kvh * G + qi % G) * nsplit + split) * (HD + 2);
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) {
+        *(float2*)(dst + 16 * dt + 4 * g) = make_float2(o[b][dt][0], o[b][dt][1]);
+        *(float2*)(dst + 16 * dt + 4 * g + 2) = make_float2(o[b][dt][2], o[b][dt][3]);
+      }
+      if (g == 0) *(float2*)(dst + HD) = make_float2(m_run[b] * 0.6931471805599453f, l_run[b]);
     }
   }
 }
@@ -1286,13 +1346,17 @@ void attn_split(const AttnArgs& a, hipStream_t st) {
 #undef KS_DEC_S
 #undef KS_DEC
   } else if (a.hd == 128 && a.tiles > 1) {
-    // batched rows: matrix-instruction kernel, 64 query vectors per workgroup
-    const int span = TILE * a.tiles;
-    constexpr int QWG = 16 * KS_BAT_NW * KS_BAT_CB;  // query vectors per workgroup
-    dim3 g2((a.max_len + span - 1) / span, a.hkv, (a.M * G + QWG - 1) / QWG);
-    KS_LAUNCH((k_attn_bat<KS_BAT_NW, KS_BAT_ST, KS_BAT_CB>), g2, dim3(64 * KS_BAT_NW), 0,
-              st, a.M, a.hq, a.hkv, a.n_max, a.q, (const bf16_t*)a.kc,
-              (const bf16_t*)a.vc, a.len, a.max_len, span, a.part, a.nsplit);
+    // batched rows: two column blocks per wave where their workgroups fill the
+    // chip twice over, else one (625 rows over 8192: 165 us against 176; 100
+    // rows: 46 against 40; 213 rows over 1237: 44 against 33)
+    auto blocks = [&](int cb) { return (unsigned)((a.M * G + 64 * cb - 1) / (64 * cb)) * a.hkv * ns; };
+#define KS_BAT(CB_)                                                                             \
+  KS_LAUNCH(k_attn_bat<CB_>, dim3(blocks(CB_)), dim3(256), 0, st, a.M, a.hq, a.hkv, a.n_max,    \
+            a.q, (const bf16_t*)a.kc, (const bf16_t*)a.vc, a.len, a.max_len, a.span, a.part,    \
+            a.nsplit)
+    if (blocks(2) >= 512) KS_BAT(2);
+    else KS_BAT(1);
+#undef KS_BAT
   } else if (a.hd == 128) {
     if (nq <= 4) KS_ATTN(128, true, 1); else KS_ATTN(128, true, 8);
   } else {

@@ -95,3 +95,38 @@ def test_prefill_passes_keep_the_bits_of_single_chunks(edges):
     assert runs[0][0] == runs[1][0]
     for a, b in zip(runs[0][1], runs[1][1]):
         assert torch.equal(a, b)
+
+
+@pytest.fixture(scope="module")
+def long_ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd.engine import DeviceModel
+    cfg = dataclasses.replace(W.config("small_qwen_bf16"), L=1)
+    w = W.generate_weights(cfg, seed=0)
+    dm = DeviceModel(cfg, n_max=6400, gamma_max=4, m_rounds=5, cap_max=128,
+                     prefill_chunk=64).upload_all(w)
+    yield cfg, dm, M.Model(cfg, w)
+    dm.close()
+
+
+# 17, 33 and 130 rows x 4 heads: the last workgroup of 64 query vectors holds 4, 4
+# and 8 (one column block per wave); 1270 rows at 6200 positions: 40 x 2 x 7
+# workgroups of 128 vectors, the last one 88 full (two blocks per wave)
+@pytest.mark.parametrize("R,n", [(R, n) for R in (17, 33, 130) for n in (1, 63, 65, 1024, 2049)] +
+                         [(1270, 6200)])
+def test_batched_attention_edges(long_ctx, R, n):
+    """Lengths at the edges of a 64-key tile and of a 1024-position split; row
+    lengths differ (position 0 rows see only their own key); keys past the
+    cached ones are NaN and must not be read into a result."""
+    cfg, dm, model = long_ctx
+    cache = fill_layer(cfg, dm, 0, n, 6400)
+    for t in dm.kv_layer(0):
+        t[:, n:] = float("nan")
+    pos = (n - np.arange(R) % min(n + 1, 70)).astype(np.int32)
+    x = W.synthetic_rows(R, cfg.d, seed=4, std=0.5, index=40 + R)
+    out = torch.empty(R, cfg.d, device="cuda")
+    dm.sublayer_apply(1, torch.from_numpy(x).cuda(), pos, mode=1, out=out)
+    s = np.arange(R) if R < 1000 else np.r_[0:40, 600:640, R - 40:R]
+    ref = M.sublayer(model, 1, x[s].astype(np.float64), pos[s], cache, mode="own")
+    check_rows(out.cpu().numpy()[s], x[s], ref, TOL, ("attention", R, n))

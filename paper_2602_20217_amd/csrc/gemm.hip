@@ -922,56 +922,98 @@ void gemm_bf16_tiled(const GemmArgs& g, hipStream_t st) {
 }
 
 // --------------------------------------------------------------------- f32
-// Plain 16x16 LDS tiles, k ascending; used only by float32 models.
-// EPI_SWIGLU: W is [gate rows; up rows], Nout = N/2 outputs.
+// float32 models: 16 x 16 outputs per workgroup of eight waves, on the float32
+// matrix instruction (16x16x4, float32 products and sums).  Wave w takes the
+// 16-wide k groups [w KG / 8, (w + 1) KG / 8), four instructions per group, and
+// the eight partial sums are added in wave order, so a row's result does not
+// depend on the other rows.  Both operands go straight to registers: lane
+// (j, g) loads k 16 s + 4 g .. + 3 of row j, and instruction e of a group takes
+// element e of every lane.  These products are bound by latency: at 5 rows the
+// down projection of the tiny decoder (K = 1024, 16 workgroups) spent 31 us in 64
+// dependent rounds of load, barrier and 16 multiply-adds; now all of a wave's
+// loads are in flight together: 5 us (gate/up 12 -> 5, q/k/v 9.4 -> 4).
+// vec: the weights are 16-byte aligned.
+// EPI_SWIGLU: W is [gate rows; up rows], Nout = N/2 outputs.  Nout % 16 == 0,
+// K % 16 == 0.
+constexpr int F32_NW = 8;
 template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(int M, int Nout, int K,
-                                                  const float* __restrict__ A, int lda,
-                                                  const float* __restrict__ W, float* out,
-                                                  int ldo, const float* res, int ldres,
-                                                  float* aout, int ldact) {
-  __shared__ float As[16][17], Ws[16][17], Us[16][17];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int mb = blockIdx.y * 16, nb = blockIdx.x * 16;
-  float acc = 0.f, accu = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    As[ty][tx] = (mb + ty < M) ? A[(size_t)(mb + ty) * lda + k0 + tx] : 0.f;
-    Ws[ty][tx] = (nb + ty < Nout) ? W[(size_t)(nb + ty) * K + k0 + tx] : 0.f;
-    if (EPI == EPI_SWIGLU)
-      Us[ty][tx] = (nb + ty < Nout) ? W[(size_t)(Nout + nb + ty) * K + k0 + tx] : 0.f;
-    __syncthreads();
+__global__ __launch_bounds__(64 * F32_NW) void k_gemm_f32(int M, int Nout, int K,
+                                                          const float* __restrict__ A, int lda,
+                                                          const float* __restrict__ W, float* out,
+                                                          int ldo, const float* res, int ldres,
+                                                          float* aout, int ldact, int vec) {
+  constexpr int NW = F32_NW, U = 4, NP = EPI == EPI_SWIGLU ? 2 : 1;
+  __shared__ f32x4 red[NP][NW][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+  const int KG = K >> 4;
+  const int kb = (wave * KG) / NW, ke = ((wave + 1) * KG) / NW;
+  const float* src[1 + NP];  // row m0 + j of A (clamped: rows past M are not stored), of W
+  src[0] = A + (size_t)min(m0 + j, M - 1) * lda + 4 * g;
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      acc = fmaf(As[ty][kk], Ws[tx][kk], acc);
-      if (EPI == EPI_SWIGLU) accu = fmaf(As[ty][kk], Us[tx][kk], accu);
-    }
-    __syncthreads();
+  for (int p = 0; p < NP; ++p) src[1 + p] = W + (size_t)(p * Nout + n0 + j) * K + 4 * g;
+  auto load = [&](const float* p) {
+    if (vec) return *(const f32x4*)p;
+    return f32x4{p[0], p[1], p[2], p[3]};
+  };
+  f32x4 acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k = kb; k < ke; k += U) {
+    f32x4 x[1 + NP][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p <= NP; ++p) x[p][u] = load(src[p] + 16 * min(k + u, ke - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k + u < ke) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int p = 0; p < NP; ++p)
+            acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][u][e], x[1 + p][u][e], acc[p], 0, 0, 0);
+      }
   }
-  const int m = mb + ty, n = nb + tx;
-  if (m >= M || n >= Nout) return;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) red[p][wave][lane] = acc[p];
+  __syncthreads();
+  // thread: lane l, register v of the result tile (row 4 (l / 16) + v, column l % 16)
+  const int l = threadIdx.x >> 2, v = threadIdx.x & 3;
+  const int m = m0 + 4 * (l >> 4) + v, n = n0 + (l & 15);
+  if (l >= 64 || m >= M) return;
+  float s[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    s[p] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s[p] += red[p][w][l][v];
+  }
   if (EPI == EPI_SWIGLU) {
-    aout[(size_t)m * ldact + n] = silu_mul(acc, accu);
+    aout[(size_t)m * ldact + n] = silu_mul(s[0], s[NP - 1]);
   } else {
-    if (EPI == EPI_RESID) acc += res[(size_t)m * ldres + n];
-    out[(size_t)m * ldo + n] = acc;
+    if (EPI == EPI_RESID) s[0] += res[(size_t)m * ldres + n];
+    out[(size_t)m * ldo + n] = s[0];
   }
 }
 
 void gemm_f32(const GemmArgs& g, hipStream_t st) {
   const int Nout = g.epi == EPI_SWIGLU ? g.N / 2 : g.N;
-  dim3 grid((Nout + 15) / 16, (g.M + 15) / 16);
+  const dim3 grid(Nout / 16, (g.M + 15) / 16), block(64 * F32_NW);
   const float* A = (const float*)g.A.hi;
   const float* W = (const float*)g.W;
+  const int vec = (((uintptr_t)A | (uintptr_t)W) & 15) == 0 && g.A.ld % 4 == 0;
   if (g.epi == EPI_SWIGLU)
-    KS_LAUNCH(k_gemm_f32<EPI_SWIGLU>, grid, dim3(256), 0, st, g.M, Nout, g.K, A,
-              g.A.ld, W, g.out, g.ldo, g.res, g.ldres, (float*)g.act_out.hi,
-              g.act_out.ld);
+    KS_LAUNCH(k_gemm_f32<EPI_SWIGLU>, grid, block, 0, st, g.M, Nout, g.K, A, g.A.ld, W, g.out,
+              g.ldo, g.res, g.ldres, (float*)g.act_out.hi, g.act_out.ld, vec);
   else if (g.epi == EPI_RESID)
-    KS_LAUNCH(k_gemm_f32<EPI_RESID>, grid, dim3(256), 0, st, g.M, Nout, g.K, A, g.A.ld,
-              W, g.out, g.ldo, g.res, g.ldres, nullptr, 0);
+    KS_LAUNCH(k_gemm_f32<EPI_RESID>, grid, block, 0, st, g.M, Nout, g.K, A, g.A.ld, W, g.out,
+              g.ldo, g.res, g.ldres, nullptr, 0, vec);
   else
-    KS_LAUNCH(k_gemm_f32<EPI_STORE>, grid, dim3(256), 0, st, g.M, Nout, g.K, A, g.A.ld,
-              W, g.out, g.ldo, g.res, g.ldres, nullptr, 0);
+    KS_LAUNCH(k_gemm_f32<EPI_STORE>, grid, block, 0, st, g.M, Nout, g.K, A, g.A.ld, W, g.out,
+              g.ldo, g.res, g.ldres, nullptr, 0, vec);
 }
 
 // ----------------------------------------------------------------- packing

@@ -130,3 +130,40 @@ def test_batched_attention_edges(long_ctx, R, n):
     s = np.arange(R) if R < 1000 else np.r_[0:40, 600:640, R - 40:R]
     ref = M.sublayer(model, 1, x[s].astype(np.float64), pos[s], cache, mode="own")
     check_rows(out.cpu().numpy()[s], x[s], ref, TOL, ("attention", R, n))
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_f32_products_edges(shift):
+    """float32 products with fewer k groups than waves (d = 96: 6 groups for 8
+    waves), a ragged last row tile and (shift 1) weights that are only 4-byte
+    aligned; rows of one launch equal the same rows alone."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd.engine import DeviceModel
+    cfg = dataclasses.replace(W.config("tiny"), name="edges_f32", L=1, d=96, hq=2, hkv=1, ffn=160,
+                              vocab=1040)
+    w = W.generate_weights(cfg, seed=0)
+    dm = DeviceModel(cfg, n_max=64, gamma_max=4, m_rounds=5, cap_max=64, prefill_chunk=16)
+    for k in ("wqkv", "wo", "w_gate_up", "w_down"):
+        t = dm.w[k][0]
+        dm.w[k][0] = torch.empty(t.numel() + shift, device="cuda")[shift:].view(t.shape)
+    t = dm.w["lm_head"]
+    dm.w["lm_head"] = torch.empty(t.numel() + shift, device="cuda")[shift:].view(t.shape)
+    dm.upload_all(w)
+    model = M.Model(cfg, w)
+    R, n = 21, 10
+    cache = fill_layer(cfg, dm, 0, n, 64)
+    x = W.synthetic_rows(R, cfg.d, seed=4, std=0.5, index=7)
+    pos = (np.arange(R) % n).astype(np.int32)
+    for i in (1, 2):
+        out, one = torch.empty(R, cfg.d, device="cuda"), torch.empty(1, cfg.d, device="cuda")
+        xd = torch.from_numpy(x).cuda()
+        dm.sublayer_apply(i, xd, pos, mode=1, out=out)
+        ref = M.sublayer(model, i, x.astype(np.float64), pos, cache, mode="own")
+        check_rows(out.cpu().numpy(), x, ref, 1e-4, ("f32", shift, i))
+        if i == 2:  # (one row takes the decode attention, another split)
+            dm.sublayer_apply(i, xd[17:18].contiguous(), pos[17:18], mode=1, out=one)
+            assert torch.equal(one[0], out[17])
+    logits, _, _ = dm.head_rows(torch.from_numpy(x).cuda())
+    assert rel_err(logits.cpu().numpy(), M.head(model, x.astype(np.float64))[0]) < 1e-4
+    dm.close()

@@ -414,15 +414,115 @@ static void launch_skinny(const GemmArgs& g, hipStream_t st) {
   else launch_skinny_an<NB, NW, CH, MINB, 0, STAGE>(g, st);
 }
 
+static int compute_units() {
+  static std::atomic<int> cached[16];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return 256;
+  int n = cached[dev].load(std::memory_order_relaxed);
+  if (n <= 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        n <= 0)
+      n = 256;
+    cached[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
+// Vocabulary head on up to 8 rows: the arithmetic of k_gemm_skinny<1, 8, 4, ..>
+// (EPI_STORE, AN = 1, same waves, k order and sums: the same bits) with workgroups
+// that stay and walk the weight tiles blockIdx.x, + gridDim.x, ...  With one tile
+// per workgroup every one of the 8016 (128256 rows) reads its rows' activation
+// fragments again, as many bytes as its weights at 7 rows, and pays a start and an
+// end; here a wave keeps the fragments of its KS k steps in registers for all its
+// tiles, and the next tile's weights are requested before the current one's matrix
+// instructions.  The tile's partial sums meet in one of two LDS buffers, so one
+// barrier per tile orders both, and it waits for LDS only.
+// Bound by the weight stream.  Final norm, head and argmax of the 128256-row head:
+// 4 / 5 / 8 rows 186 / 198 / 237 -> 180 / 185 / 190 us (one row 172); up to 3 rows
+// one tile per workgroup is the faster (2 rows: 172 against 181 us).
+template <int KS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_head(
+    int M, int N, int K, const bf16_t* __restrict__ Ahi, const bf16_t* __restrict__ Alo, int lda,
+    const bf16_t* __restrict__ Wp, float* __restrict__ out, int ldo,
+    const float* __restrict__ ssq_in, int nssq, float eps) {
+  constexpr int NW = 8;
+  __shared__ f32x4 red[2][NW][64];
+  __shared__ float s_rs[8];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KT = K >> 5, NT = N >> 4;
+  const int slot = lane & 15, plane = slot >> 3, kg = lane >> 4;
+  const int r = (slot & 7) < M ? slot & 7 : 0;
+  const bf16_t* wb = Wp + (size_t)wave * KS * 512 + lane * 8;
+  bf16x8 x[KS], w[2][KS];
+  auto fetch = [&](int nt, bf16x8 (&f)[KS]) {
+#pragma unroll
+    for (int u = 0; u < KS; ++u) f[u] = ld_frag_nt(wb + ((size_t)nt * KT + u) * 512);
+  };
+  int nt = blockIdx.x;
+  fetch(nt, w[0]);
+  {
+    const bf16_t* ap = (plane ? Alo : Ahi) + (size_t)r * lda + (wave * KS) * 32 + kg * 8;
+#pragma unroll
+    for (int u = 0; u < KS; ++u) x[u] = ld_frag(ap + u * 32);
+  }
+  if (wave < M) {  // row sums as in k_gemm_skinny
+    float t = 0.f;
+    for (int j = lane; j < nssq; j += 64) t += ssq_in[(size_t)wave * nssq + j];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+    if (lane == 0) s_rs[wave] = 1.0f / sqrtf(t / (float)K + eps);
+  }
+  // output of this thread: row em, column el % 16 of the tile
+  const int el = (threadIdx.x >> 2) & 31, ev = threadIdx.x & 3;
+  const int em = 4 * (el >> 4) + ev;
+  const bool eact = threadIdx.x < 128 && em < M;
+  auto tile = [&](auto buf_) {
+    constexpr int buf = decltype(buf_)::value;
+    const int next = nt + gridDim.x;
+    if (next < NT) fetch(next, w[buf ^ 1]);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u], w[buf][u], acc, 0, 0, 0);
+    red[buf][wave][lane] = acc;
+    __asm__ volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS accesses are done
+    __builtin_amdgcn_s_barrier();
+    __asm__ volatile("" ::: "memory");
+    if (eact) {
+      float a = 0.f, b = 0.f;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        a += red[buf][q][el][ev];
+        b += red[buf][q][el + 32][ev];
+      }
+      out[(size_t)em * ldo + nt * 16 + (el & 15)] = (a + b) * s_rs[em];
+    }
+    nt = next;
+    return next < NT;
+  };
+  while (tile(std::integral_constant<int, 0>{}) && tile(std::integral_constant<int, 1>{})) {
+  }
+}
+
+template <int KS>
+static void launch_head(const GemmArgs& g, hipStream_t st) {
+  KS_LAUNCH(k_gemm_head<KS>, dim3(std::min(g.N / 16, compute_units())), dim3(512), 0, st, g.M, g.N,
+            g.K, (const bf16_t*)g.A.hi, (const bf16_t*)g.A.lo, g.A.ld, (const bf16_t*)g.W, g.out,
+            g.ldo, g.ssq_in, g.nssq, g.eps);
+}
+
 // Launch shape by matrix shape only (never by row count; the one-row staging
 // changes where the operands come from, not the arithmetic), measured on
 // MI355X with the Llama-8B shapes (cold weights; 4/8/16 waves, 1/2/4-deep
 // pipelined chunks, workgroups per CU forced by the register budget, staging
 // on or off): gate/up one tile per 4-wave workgroup, 2-deep chunks; the long-K
 // down projection and the square O projection 16 waves, 4-deep; the vocabulary
-// head and the q/k/v projection 8 waves, 4-deep; every shape with the one-row
-// activation staged in LDS and two chunks per wave in flight from the start
-// (8K decode step 3.22 -> 3.09 ms against per-step activation loads).
+// head and the q/k/v projection 8 waves, 4-deep; every shape but the head with the
+// one-row activation staged in LDS and two chunks per wave in flight from the start
+// (8K decode step 3.22 -> 3.09 ms against per-step activation loads).  The head's
+// 8016 workgroups pay the staging each: 180 us with it, 171.5 without.
 // (output tiles per workgroup, waves, k steps per chunk, workgroups per CU
 // the register budget must allow, one-row activation staged in LDS)
 #ifndef KS_SK_GU
@@ -432,7 +532,7 @@ static void launch_skinny(const GemmArgs& g, hipStream_t st) {
 #define KS_SK_DOWN 1, 16, 4, 1, 1
 #endif
 #ifndef KS_SK_HEAD
-#define KS_SK_HEAD 1, 8, 4, 1, 1
+#define KS_SK_HEAD 1, 8, 4, 1, 0
 #endif
 #ifndef KS_SK_SQ
 #define KS_SK_SQ 1, 16, 4, 1, 1
@@ -443,7 +543,15 @@ static void launch_skinny(const GemmArgs& g, hipStream_t st) {
 void gemm_bf16_skinny(const GemmArgs& g, hipStream_t st) {
   if (g.epi == EPI_SWIGLU) launch_skinny<KS_SK_GU>(g, st);
   else if (g.K >= 8192) launch_skinny<KS_SK_DOWN>(g, st);
-  else if (g.N >= 65536) launch_skinny<KS_SK_HEAD>(g, st);
+  else if (g.N >= 65536 && g.M >= 4 && g.M <= 8 && g.ssq_in && g.epi == EPI_STORE &&
+           g.K % 1024 == 0 && g.K <= 4096) {
+    switch (g.K / 1024) {  // k steps per wave: K / 256
+      case 1: launch_head<4>(g, st); break;
+      case 2: launch_head<8>(g, st); break;
+      case 3: launch_head<12>(g, st); break;
+      default: launch_head<16>(g, st); break;
+    }
+  } else if (g.N >= 65536) launch_skinny<KS_SK_HEAD>(g, st);
   else if (g.N <= 4096) launch_skinny<KS_SK_SQ>(g, st);
   else launch_skinny<KS_SK_WIDE>(g, st);
 }
@@ -780,20 +888,6 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(int M, int N, int SK,
     s.x = r.x + s.x; s.y = r.y + s.y; s.z = r.z + s.z; s.w = r.w + s.w;
   }
   *(float4*)&out[(size_t)m * ldo + n] = s;
-}
-
-static int compute_units() {
-  static std::atomic<int> cached[16];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return 256;
-  int n = cached[dev].load(std::memory_order_relaxed);
-  if (n <= 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        n <= 0)
-      n = 256;
-    cached[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
 }
 
 // Parts of the K sum of a product over `rows` rows (see k_gemm_wide).  They set

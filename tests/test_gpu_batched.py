@@ -167,3 +167,26 @@ def test_f32_products_edges(shift):
     logits, _, _ = dm.head_rows(torch.from_numpy(x).cuda())
     assert rel_err(logits.cpu().numpy(), M.head(model, x.astype(np.float64))[0]) < 1e-4
     dm.close()
+
+
+@pytest.mark.parametrize("d", [1024, 2048])
+def test_head_rows_keep_their_bits(d):
+    """A large vocabulary (65552: 4097 tiles, one more than 16 rounds of 256
+    workgroups): 4 to 8 rows run on workgroups that walk the tiles, 1 to 3 and 9 to
+    16 on one tile each; a row's logits are the same bits in all of them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd.engine import DeviceModel
+    cfg = dataclasses.replace(W.config("small_bf16"), name="head_bf16", L=1, d=d, hq=2, hkv=1,
+                              ffn=32, vocab=65552)
+    w = W.generate_weights(cfg, seed=0)
+    dm = DeviceModel(cfg, n_max=64, gamma_max=15, cap_max=16, prefill_chunk=16).upload_all(w)
+    x = torch.from_numpy(W.synthetic_rows(12, d, seed=4, std=0.5, index=11)).cuda()
+    all_rows = dm.head_rows(x)[0]
+    for a, b in ((0, 1), (1, 4), (4, 8), (3, 8), (4, 12), (0, 7)):
+        logits, am, _ = dm.head_rows(x[a:b].contiguous())
+        assert torch.equal(logits, all_rows[a:b]), (a, b)
+        assert torch.equal(am.long(), logits.argmax(-1))
+    lg0 = M.head(M.Model(cfg, w), x[4:6].cpu().numpy().astype(np.float64))[0]
+    assert rel_err(all_rows[4:6].cpu().numpy(), lg0) < TOL
+    dm.close()

@@ -1266,10 +1266,12 @@ __global__ __launch_bounds__(256) void k_attn_combine(int M, int hq, int hkv, in
     uint32_t hp = 0, lp = 0;
 #pragma unroll
     for (int e = 0; e < DPL; ++e) {
-      const float v = acc[e] * inv;
-      const bf16_t hi = f2bf(v);
+      // the low plane rounds the remainder of the exact product: written as one
+      // fused operation, as whether the compiler fuses it by itself depends on the
+      // code around (it does not where the subtraction sits behind `if (olo)`)
+      const bf16_t hi = f2bf(acc[e] * inv);
       hp |= (uint32_t)hi << (16 * e);
-      lp |= (uint32_t)f2bf(v - bf2f(hi)) << (16 * e);
+      lp |= (uint32_t)f2bf(fmaf(acc[e], inv, -bf2f(hi))) << (16 * e);
     }
     if (DPL == 2) {
       *(uint32_t*)&ohi[off] = hp;

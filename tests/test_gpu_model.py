@@ -433,3 +433,40 @@ def test_head_cost_selections_and_intervals(setup):
                                           sref.exec_mask)
             assert (sg.j_star, sg.gamma_star) == (sref.j_star, sref.gamma_star)
             assert sg.tpt_star == pytest.approx(sref.tpt_star, rel=1e-12)
+
+
+@pytest.mark.parametrize("R", [1, 5, 12])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_attention_merge_planes(R, mode):
+    """The attention rows that feed the O projection on decode and verify rows are
+    hi + lo bf16 planes of acc / l: hi rounds the float32 quotient, lo the exact
+    remainder of acc * (1 / l) (one fused operation, not the difference of the
+    rounded quotient).  Rows of zeros give zero queries, keys and values, so every
+    cached position has weight 1; with cached values that are multiples of 1 / 64
+    acc is exact, and an identity O projection returns the float32 sum hi + lo."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import dataclasses
+
+    from paper_2602_20217_amd.engine import DeviceModel
+    cfg = dataclasses.replace(W.config("small_bf16"), L=1)
+    assert cfg.d == cfg.hq * cfg.hd
+    n = 300
+    w = W.generate_weights(cfg, seed=0)
+    w[("wo", 0)] = np.eye(cfg.d, dtype=np.float32)
+    dm = DeviceModel(cfg, n_max=400, gamma_max=15, cap_max=16, prefill_chunk=16).upload_all(w)
+    v = np.random.default_rng(n).integers(-128, 128, (cfg.hkv, n, cfg.hd))
+    kk, vv = dm.kv_layer(0)
+    vv[:, :n] = torch.from_numpy(v).cuda() / 64.0
+    pos = n + np.arange(R) if mode == 0 else np.full(R, n)
+    out = torch.empty(R, cfg.d, device="cuda")
+    dm.sublayer_apply(1, torch.zeros(R, cfg.d, device="cuda"), pos, mode=mode, out=out)
+    bf = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().double().numpy()
+    acc = np.repeat(v.sum(1) / 64.0, cfg.hq // cfg.hkv, axis=0).reshape(-1)
+    inv = (np.float32(1) / (pos + 1).astype(np.float32)).astype(np.float64)[:, None]
+    q = acc * inv  # exact: 16-bit by 24-bit factors
+    hi = bf(q)
+    fused, twice = ((hi + bf(r)).astype(np.float32) for r in (q - hi, q.astype(np.float32) - hi))
+    assert (fused != twice).any()  # the two ways of forming lo differ at these values
+    assert int((out.cpu().numpy() != fused).sum()) == 0
+    dm.close()

@@ -850,12 +850,20 @@ __device__ inline float sum_x32(float v) {
       __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// 16 bytes per lane from base + off straight into LDS at byte `lds` + 16 lane.
+// byte address of an array in LDS
+__device__ inline uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+// 16 bytes per lane from base + off straight into LDS at byte `lds` + 16 lane
+// (lds: from lds_addr of the array that is filled, which also tells the compiler
+// that the block writes it).
 // Written out so that the compiler, which cannot tell the ring's stages apart,
 // puts no wait for it before LDS reads; the kernel counts its own waits.  (No
-// register is written, so none can be overwritten late.)
+// register is written, so none can be overwritten late.)  The compiler places no
+// wait states inside the block: the move and s_nop 3 are the one that m0 needs
+// and the five that a scalar base written by the vector unit (a spilled one) needs.
 __device__ inline void load_lds16(const void* base, uint32_t off, uint32_t lds) {
-  __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+  __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                    :
                    : "v"(off), "s"(base), "s"(lds)
                    : "memory", "m0");
@@ -933,10 +941,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
   for (int u = 0; u < PPW; ++u) ck[u] = ((lane & 15) ^ ((pr + 4 * u) & 15)) << 4;
   const uint32_t cv = ((lane & 15) ^ (2 * (pr & 7))) << 4;  // piece u: cv ^ 128 (u % 2)
+  const uint32_t lds0 = lds_addr(KV);
   auto issue = [&](int t0, int buf) {
     const int lastrow = max_len - 1 - t0;
     const size_t to = (size_t)t0 * (HD * 2);
-    const uint32_t at = 2 * buf * SB + 1024 * PPW * w;
+    const uint32_t at = lds0 + 2 * buf * SB + 1024 * PPW * w;
 #pragma unroll
     for (int u = 0; u < PPW; ++u)
       load_lds16(kb + to, ((uint32_t)min(pr + 4 * u, lastrow) << 8) + ck[u], at + 1024 * u);

@@ -868,6 +868,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
+// four floats at any float's address (callers' logits and rows)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // out[m][n] = (res[m][n] +) sum over ks in order of part[ks][m][n]; N % 4 == 0
 template <int EPI>
 __global__ __launch_bounds__(256) void k_splitk_reduce(int M, int N, int SK,
@@ -878,16 +881,10 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(int M, int N, int SK,
   const int n4 = N >> 2;
   if (i4 >= (size_t)M * n4) return;
   const int m = (int)(i4 / n4), n = (int)(i4 % n4) * 4;
-  float4 s = *(const float4*)&part[(size_t)m * N + n];
-  for (int k = 1; k < SK; ++k) {
-    const float4 t = *(const float4*)&part[((size_t)k * M + m) * N + n];
-    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-  }
-  if (EPI == EPI_RESID) {
-    const float4 r = *(const float4*)&res[(size_t)m * ldres + n];
-    s.x = r.x + s.x; s.y = r.y + s.y; s.z = r.z + s.z; s.w = r.w + s.w;
-  }
-  *(float4*)&out[(size_t)m * ldo + n] = s;
+  f32x4 s = *(const f32x4*)&part[(size_t)m * N + n];
+  for (int k = 1; k < SK; ++k) s += *(const f32x4*)&part[((size_t)k * M + m) * N + n];
+  if (EPI == EPI_RESID) s = *(const f32x4_any*)&res[(size_t)m * ldres + n] + s;
+  *(f32x4_any*)&out[(size_t)m * ldo + n] = s;
 }
 
 // Parts of the K sum of a product over `rows` rows (see k_gemm_wide).  They set

@@ -45,3 +45,21 @@ def test_lds_loads_in_asm_name_their_array(tmp_path):
                 left += re.findall(r"%[\w.]+", defs.get(v, ""))
             assert "ptrtoint (ptr addrspace(3) @" in text, (asm, args)
     assert seen > 0
+
+
+def test_split_sums_take_rows_at_any_float_address(tmp_path):
+    """Residual rows in and rows or logits out are the caller's, at any float's
+    address, whichever way a batched product is split; only the partial sums lie in
+    the workspace.  (The GPU tolerates a 16-byte access there, so no result shows a
+    kernel that claims 16-byte alignment of them.)"""
+    ir = _device_ir("gemm.hip", tmp_path)
+    bodies = [b for b in re.split(r"^define ", ir, flags=re.M)[1:]
+              if "k_splitk_reduce" in b.split("\n", 1)[0]]
+    assert len(bodies) == 2  # plain and with a residual
+    for body in bodies:
+        body = body.split("\n}", 1)[0]
+        stores = re.findall(r"store .* ptr addrspace\(1\) %\S+, align (\d+)", body)
+        assert stores and set(stores) == {"4"}, stores
+        loads = re.findall(r"= load <4 x float>, ptr addrspace\(1\) %\S+, align (\d+)", body)
+        resid = "ILi1E" in body.split("\n", 1)[0]  # EPI_RESID
+        assert ("4" in loads) == resid, loads

@@ -59,6 +59,26 @@ def test_sublayers(edges, R):
 
 
 @pytest.mark.parametrize("R", ROWS)
+def test_sublayers_on_rows_at_any_float_address(edges, R):
+    """Rows in and out at addresses that are multiples of 4 bytes only: the bits of
+    aligned rows, whether the products are split, folded or neither."""
+    dm, _ = edges
+    n = 90
+    fill_layer(CFG, dm, 0, n, 320)
+    x = torch.from_numpy(W.synthetic_rows(R, CFG.d, seed=4, std=0.5, index=800 + R)).cuda()
+    pos = (np.arange(R) % n).astype(np.int32)
+    at = lambda s: torch.full((R * CFG.d + 8,), 7.0, device="cuda")[s:s + R * CFG.d].view(R, -1)
+    for i in (1, 2):
+        out, x1, out1 = torch.empty_like(x), at(1), at(3)
+        x1.copy_(x)
+        dm.sublayer_apply(i, x, pos, mode=1, out=out)
+        dm.sublayer_apply(i, x1, pos, mode=1, out=out1)
+        assert torch.equal(out, out1)
+        whole = torch.as_strided(out1, (R * CFG.d + 8,), (1,), 0)
+        assert bool((whole[:3] == 7).all() and (whole[3 + R * CFG.d:] == 7).all())
+
+
+@pytest.mark.parametrize("R", ROWS)
 def test_head(edges, R):
     dm, model = edges
     x = torch.from_numpy(W.synthetic_rows(R, CFG.d, seed=4, std=0.5, index=900 + R)).cuda()

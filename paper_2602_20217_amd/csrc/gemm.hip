@@ -942,6 +942,13 @@ static WidePick wide_pick(const GemmArgs& g, int P) {
   constexpr double WIDE_LAUNCH = 4.8, WIDE_SPLIT = 2.2, WIDE_BYTES = 4.9e6;
   const int cus = compute_units();
   WidePick best{-1, MODE_ONE};
+  // One row tile by more than a round of 128 x 128 tiles (a vocabulary): bound by
+  // the weight stream, which the costs above do not hold.  Two workgroups per CU
+  // that start and end apart keep it going: final norm, head and argmax of 17 / 64 /
+  // 96 / 128 rows 230 / 241 / 252 / 265 us at 128256 columns against 235 / 250 / 261 /
+  // 272 in 128 x 256 tiles (151936 columns, 96 rows: 295 against 322).  At 129 rows
+  // it is the other way (399 against 271 in 192 x 256 tiles).
+  if (P == 1 && g.M <= 128 && (g.N / 16 + 7) / 8 > 2 * cus) return WidePick{0, MODE_ONE};
   double tb = 0.0;
   for (int i = 0; i < 4; ++i) {
     const WideShape& w = WIDE[i];

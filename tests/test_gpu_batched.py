@@ -210,3 +210,26 @@ def test_head_rows_keep_their_bits(d):
     lg0 = M.head(M.Model(cfg, w), x[4:6].cpu().numpy().astype(np.float64))[0]
     assert rel_err(all_rows[4:6].cpu().numpy(), lg0) < TOL
     dm.close()
+
+
+def test_head_rows_of_one_row_tile():
+    """65552 columns: up to 128 rows take 128 x 128 tiles, the last of them with one
+    column tile of eight, 129 rows a wider tile; a row's logits are the same bits
+    in all of them (32 rows and more: no K split at 1024)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd.engine import DeviceModel
+    cfg = dataclasses.replace(W.config("small_bf16"), name="head_bf16", L=1, d=1024, hq=2, hkv=1,
+                              ffn=32, vocab=65552)
+    w = W.generate_weights(cfg, seed=0)
+    dm = DeviceModel(cfg, n_max=64, gamma_max=15, cap_max=16, prefill_chunk=16).upload_all(w)
+    x = torch.from_numpy(W.synthetic_rows(300, 1024, seed=4, std=0.5, index=12)).cuda()
+    all_rows = dm.head_rows(x)[0]
+    for a, b in ((0, 32), (5, 69), (100, 228), (100, 229)):
+        logits, am, _ = dm.head_rows(x[a:b].contiguous())
+        assert torch.equal(logits, all_rows[a:b]), (a, b)
+        assert torch.equal(am.long(), logits.argmax(-1))
+    s = [0, 16, 127, 128, 299]
+    lg0 = M.head(M.Model(cfg, w), x[s].cpu().numpy().astype(np.float64))[0]
+    assert rel_err(all_rows[s].cpu().numpy(), lg0) < TOL
+    dm.close()

@@ -1,10 +1,19 @@
 """The batched products (k_gemm_wide) at the edges of their tiles, k steps and K
 parts: a one-layer bf16 decoder whose widths leave remainders everywhere
 (d = 4128: 129 k tiles, so steps, parts and folds end in half steps; ffn = 2880;
-vocab = 16048: 1003 column tiles).  By row count the LM head (STORE) takes 128 x
-128 tiles in 8 parts, 192 x 256 tiles in 4 and 128 x 256 tiles unsplit and with
-3 folded parts; the other products take the remaining shapes.  Sampled rows
-against the float64 oracle at the bf16 tolerance of the other tests (2e-2:
+vocab = 16048: 1003 column tiles).  By row count (256 CUs) the products take every
+tile shape, unsplit and split or folded, with ragged rows and columns:
+  LM head (STORE)    128 x 128 in 8 parts (17 rows), 192 x 256 in 4 (130), 128 x 256
+                     unsplit (300) and with 3 folded parts (520), 192 x 256 (700,
+                     1500, 2100) and 256 x 256 (2500, 3000) unsplit
+  gate/up (SWIGLU)   128 x 128 up to 520 rows, 128 x 256 (700), 192 x 256 (1500,
+                     2100, 3000), 256 x 256 (2500)
+  O (RESID)          128 x 128 unsplit up to 1500 rows, 192 x 256 (2100, 2500), 256 x
+                     256 (3000)
+  down (RESID)       split 128 x 128, 128 x 256 and 256 x 256 (17, 130, 700), unsplit
+                     128 x 256, 192 x 256, 256 x 256 (1500, 2100, 3000)
+  q/k/v (STORE)      split 128 x 128 up to 700 rows, split 128 x 256 above
+Sampled rows against the float64 oracle at the bf16 tolerance of the other tests (2e-2:
 activations are rounded to bf16 once per product, 2^-9 relative each)."""
 import dataclasses
 
@@ -21,7 +30,7 @@ torch = pytest.importorskip("torch")
 TOL = 2e-2
 CFG = dataclasses.replace(W.config("small_bf16"), name="edges_bf16", L=1, d=4128, hq=2, hkv=1,
                           ffn=2880, vocab=16048)
-ROWS = [17, 130, 300, 520, 700]
+ROWS = [17, 130, 300, 520, 700, 1500, 2100, 2500, 3000]
 
 
 @pytest.fixture(scope="module")
@@ -31,7 +40,7 @@ def edges():
     from paper_2602_20217_amd.engine import DeviceModel
     print("\n[setup] edges_bf16", flush=True)
     w = W.generate_weights(CFG, seed=0)
-    dm = DeviceModel(CFG, n_max=320, gamma_max=4, m_rounds=5, cap_max=64,
+    dm = DeviceModel(CFG, n_max=320, gamma_max=4, m_rounds=5, cap_max=80,
                      prefill_chunk=64).upload_all(w)
     yield dm, M.Model(CFG, w)
     dm.close()
@@ -117,6 +126,36 @@ def test_prefill_passes_keep_the_bits_of_single_chunks(edges):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("name", ["bf16", "f32"])
+def test_prefill_passes_keep_the_history(name):
+    """The history rows that a prefill leaves: 1036 tokens in chunks of 128 as one
+    pass of 1024 rows and a ragged chunk of 12, against one chunk at a time (limits
+    that leave room for no more).  Of the 25 history rows 13 come from the pass and 12
+    from the ragged chunk.  A selection reads them all: same record, same caches."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_20217_amd import engine as E
+    cfg = dataclasses.replace(CFG if name == "bf16" else W.config("tiny"), L=2)
+    w = W.generate_weights(cfg, seed=0)
+    n = 1036
+    prompt = W.prompt_ids(cfg.vocab, n)
+    params = E.select_params((1.0, 0.0, 1.0), "paper_min", 0, tau=0.0, D=4)  # C = 4
+    runs = []
+    for cap_max in (64, 4):
+        dm = E.DeviceModel(cfg, n_max=n + 20, gamma_max=4, m_rounds=5, cap_max=cap_max,
+                           prefill_chunk=128).upload_all(w)
+        first = dm.prefill(prompt)
+        sel, rec = dm.select(params, debug_cells=3)
+        assert sel.C == 4 and sel.n_rows == 25
+        runs.append((first, rec, [t[:, :n].clone() for l in range(2) for t in dm.kv_layer(l)]))
+        dm.close()
+    assert runs[0][0] == runs[1][0]
+    for k, v in runs[0][1].items():
+        assert np.array_equal(v, runs[1][1][k], equal_nan=v.dtype.kind == "f"), k
+    for a, b in zip(runs[0][2], runs[1][2]):
+        assert torch.equal(a, b)
+
+
 @pytest.fixture(scope="module")
 def long_ctx():
     if not torch.cuda.is_available():
@@ -189,7 +228,8 @@ def test_f32_products_edges(shift):
     dm.close()
 
 
-@pytest.mark.parametrize("d", [1024, 2048])
+# one instance of the walking kernel per d / 1024; the 8B decoders' is the last
+@pytest.mark.parametrize("d", [1024, 2048, 3072, 4096])
 def test_head_rows_keep_their_bits(d):
     """A large vocabulary (65552: 4097 tiles, one more than 16 rounds of 256
     workgroups): 4 to 8 rows run on workgroups that walk the tiles, 1 to 3 and 9 to

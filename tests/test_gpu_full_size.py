@@ -158,6 +158,17 @@ def test_full_size_head(full):
             assert am[r] == int(np.argmax(ref[r]))
 
 
+@pytest.mark.parametrize("R", [2, 4, 5, 7, 8, 9])
+def test_full_size_head_rows_equal_one_row(full, R):
+    """4 to 8 rows run on workgroups that walk the weight tiles, other counts on one
+    tile each: a row's logits are the same bits as alone."""
+    cfg, dm = full
+    x = torch.from_numpy(W.synthetic_rows(R, cfg.d, seed=4, std=1.0, index=501)).cuda()
+    logits = dm.head_rows(x)[0]
+    for r in range(R):
+        assert torch.equal(dm.head_rows(x[r:r + 1].contiguous())[0][0], logits[r]), r
+
+
 def test_full_size_decode_equals_verify(full):
     cfg, dm = full
     n = CTX - 100

@@ -68,7 +68,9 @@ typedef struct ks_limits {
   int m_rounds;       /* history keeps the last m rounds (paper: 5) */
   int cap_max;        /* largest knapsack capacity C accepted by the selection */
   int prefill_chunk;  /* rows per prefill chunk (multiple of 16): sets how the products
-                         sum; a pass runs as many whole chunks as the workspace holds */
+                         sum; a pass runs as many whole chunks, up to 4096 rows, as fit
+                         the workspace's rows, which number the larger of this chunk and
+                         (cap_max + 1) (2 m_rounds - 1) (gamma_max + 1) */
 } ks_limits;
 
 /*

@@ -1006,7 +1006,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       (uint32_t)(vrow * 256 + (((u4 >> 1) ^ (2 * (vrow & 7))) << 4) + ((u4 & 1) << 3));
 
   auto step = [&](int t0, auto buf_) {
-
     constexpr int buf = decltype(buf_)::value;
     // this wave's loads of the tile have landed; the barrier makes every wave's
     // visible and frees the other stage (its reads fed matrix instructions)

@@ -112,8 +112,10 @@ Layout make_layout(const ks_model_desc& d, const ks_limits& lim) {
   y.cells = lim.cap_max + 1;
   y.DR = y.cells * y.RING;
   y.XR = std::max(y.FR, y.DR);
-  // prefill pass: as many whole chunks as the row buffers hold anyway (the
-  // selection's candidates size them), up to PASS_MAX rows
+  // prefill pass: as many whole chunks as the row buffers hold anyway, up to
+  // PASS_MAX rows.  The selection's candidates size them, so a small cap_max leaves
+  // fewer chunks per pass (with none to spare: one at a time, same bits); the
+  // workspace does not grow for longer passes
   y.PR = std::max(lim.prefill_chunk, std::min(y.XR, PASS_MAX) / lim.prefill_chunk * lim.prefill_chunk);
   const size_t AR = align16(y.XR);  // activation rows: whole operand tiles
   y.LR = std::max(gam1, PB);

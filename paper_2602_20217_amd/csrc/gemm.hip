@@ -428,7 +428,7 @@ static int compute_units() {
   return n;
 }
 
-// Vocabulary head on up to 8 rows: the arithmetic of k_gemm_skinny<1, 8, 4, ..>
+// Vocabulary head on 4 to 8 rows: the arithmetic of k_gemm_skinny<1, 8, 4, ..>
 // (EPI_STORE, AN = 1, same waves, k order and sums: the same bits) with workgroups
 // that stay and walk the weight tiles blockIdx.x, + gridDim.x, ...  With one tile
 // per workgroup every one of the 8016 (128256 rows) reads its rows' activation
@@ -513,9 +513,10 @@ static void launch_head(const GemmArgs& g, hipStream_t st) {
             g.ldo, g.ssq_in, g.nssq, g.eps);
 }
 
-// Launch shape by matrix shape only (never by row count; the one-row staging
-// changes where the operands come from, not the arithmetic), measured on
-// MI355X with the Llama-8B shapes (cold weights; 4/8/16 waves, 1/2/4-deep
+// Launch shape by matrix shape; the row count picks only between forms that give
+// a row the same bits (staging of a single row, one or two groups of 8 rows,
+// k_gemm_head for 4 to 8 rows of a vocabulary; 9 to 16 rows of one keep a tile per
+// workgroup, as k_gemm_head's registers hold one group).  Measured on MI355X with the Llama-8B shapes (cold weights; 4/8/16 waves, 1/2/4-deep
 // pipelined chunks, workgroups per CU forced by the register budget, staging
 // on or off): gate/up one tile per 4-wave workgroup, 2-deep chunks; the long-K
 // down projection and the square O projection 16 waves, 4-deep; the vocabulary
@@ -890,9 +891,14 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(int M, int N, int SK,
 // Parts of the K sum of a product over `rows` rows (see k_gemm_wide).  They set
 // the result's bits, so they follow the sizes alone and are kept apart from the
 // tile shape and from how many rows a launch holds: a prefill pass over several
-// chunks, or another tile, gives the bits of one chunk at a time.  The count
-// comes from a cost model of 128 x 256 tiles, two workgroups per CU, that splits
-// K while the rows leave CUs idle.
+// chunks, or another tile, gives the bits of one chunk at a time.  The rule stands
+// for these bits and not for speed: it splits K while the rows leave CUs idle, by
+// the costs of a kernel of 128 x 256 tiles, two workgroups per CU and three ring
+// stages, that k_gemm_wide has replaced (us per 32-wide k step with a CU alone and
+// shared, per split launch, and bytes per us).  Counts by k_gemm_wide's own costs
+// would take 12.0 ms instead of 12.5 for 8192 tokens in chunks of 512 through two
+// layers, and 5% off a selection, at other bits: decisions of a selection that hang
+// on near ties move with them.
 static int gemm_parts(const GemmArgs& g) {
   constexpr double T_ALONE = 0.57, T_SHARED = 0.97, T_LAUNCH = 3.0, BYTES_PER_US = 4.5e6;
   if (g.epi == EPI_SWIGLU || !g.part) return 1;

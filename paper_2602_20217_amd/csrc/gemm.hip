@@ -950,11 +950,18 @@ static WidePick wide_pick(const GemmArgs& g, int P) {
   WidePick best{-1, MODE_ONE};
   // One row tile by more than a round of 128 x 128 tiles (a vocabulary): bound by
   // the weight stream, which the costs above do not hold.  Two workgroups per CU
-  // that start and end apart keep it going: final norm, head and argmax of 17 / 64 /
-  // 96 / 128 rows 230 / 241 / 252 / 265 us at 128256 columns against 235 / 250 / 261 /
-  // 272 in 128 x 256 tiles (151936 columns, 96 rows: 295 against 322).  At 129 rows
-  // it is the other way (399 against 271 in 192 x 256 tiles).
-  if (P == 1 && g.M <= 128 && (g.N / 16 + 7) / 8 > 2 * cus) return WidePick{0, MODE_ONE};
+  // that start and end apart keep it going, if their last round puts no more than
+  // one on a CU or, as the second round, nearly fills it: final norm, head and argmax
+  // of 17 / 64 / 96 / 128 rows 229 / 239 / 250 / 263 us at 128256 columns of 4096
+  // (1002 tiles) against 233 / 250 / 260 / 272 in 128 x 256 tiles; 96 rows by 151936
+  // columns (1187 tiles) 293 against 320.  With half to 4/5 of a round left (100352
+  // to 110592 columns) or in later rounds (180224, 256000) some CUs stream two tiles
+  // and others one: 5 to 10% and 1 to 5% the other way.
+  if (P == 1 && g.M <= 128) {
+    const int tiles = (g.N / 16 + 7) / 8, last = (tiles - 1) % (2 * cus) + 1;
+    if (tiles > 2 * cus && (last <= cus || (tiles < 4 * cus && 5 * last >= 8 * cus)))
+      return WidePick{0, MODE_ONE};
+  }
   double tb = 0.0;
   for (int i = 0; i < 4; ++i) {
     const WideShape& w = WIDE[i];

@@ -928,9 +928,17 @@ static int gemm_parts(const GemmArgs& g) {
 // k step of 64 while more than one workgroup per CU (at most 80 KiB of LDS) or
 // every CU is busy (full) and in a last round of at most one workgroup per CU
 // (alone), and us per round.  A launch costs WIDE_LAUNCH, a split WIDE_SPLIT and
-// P + 2 float32 planes at WIDE_BYTES per us; folding the parts in the workgroup
-// costs no traffic but needs a second set of accumulators, so only the 128 x 256
-// tile does it.
+// P + 2 float32 planes at WIDE_BYTES per us: above the memory's rate, as the
+// partials (at most 128 MiB) are summed out of the last-level cache.  One row tile
+// whose weights stream through that cache (WIDE_LLC) evicts them and pays MEM_SPLIT
+// and MEM_BYTES.  Folding the parts in the workgroup costs no traffic but needs a
+// second set of accumulators, so only the 128 x 256 tile does it.  The split's costs
+// are fitted to 310 split products (17..1200 rows, 4096..200064 columns, K 1024..8192),
+// where the pick is within 0.7% of the best form on average and 8% at worst; with
+// the memory's rate for all of them it folded too soon (1.4% and 17%), with the
+// cache's too late (1.5% and 16%).  512 rows by 6144 columns of 2048 (the head call)
+// 66.7 -> 59.2 us, 1200 by 4096 of 4096 118 -> 105; both sublayers on 700 / 1152 /
+// 1390 candidate rows 468 -> 449 / 684 -> 622 / 836 -> 774 us (Qwen, Qwen, Llama).
 struct WideShape {
   int ri, c0, c1;
   double full, alone, round;
@@ -945,7 +953,10 @@ struct WidePick {
   int shape, mode;
 };
 static WidePick wide_pick(const GemmArgs& g, int P) {
-  constexpr double WIDE_LAUNCH = 4.8, WIDE_SPLIT = 2.2, WIDE_BYTES = 4.9e6;
+  constexpr double WIDE_LAUNCH = 4.8, WIDE_SPLIT = 1.0, WIDE_BYTES = 10e6;
+  constexpr double MEM_SPLIT = 2.2, MEM_BYTES = 4.9e6;
+  constexpr size_t WIDE_LLC = (size_t)256 << 20;
+  const bool cached = g.M > 128 || (size_t)g.N * g.K * 2 <= WIDE_LLC;
   const int cus = compute_units();
   WidePick best{-1, MODE_ONE};
   // One row tile by more than a round of 128 x 128 tiles (a vocabulary): bound by
@@ -976,7 +987,8 @@ static WidePick wide_pick(const GemmArgs& g, int P) {
       for (long left = mode == MODE_SPLIT ? tiles * P : tiles; left > 0; left -= resident)
         t += w.round + steps * (left >= resident || left > cus ? w.full : w.alone);
       if (mode == MODE_SPLIT)
-        t += WIDE_SPLIT + (P + 2.0) * g.M * (double)g.N * 4.0 / WIDE_BYTES;
+        t += (cached ? WIDE_SPLIT : MEM_SPLIT) +
+             (P + 2.0) * g.M * (double)g.N * 4.0 / (cached ? WIDE_BYTES : MEM_BYTES);
       if (best.shape < 0 || t < tb) {
         tb = t;
         best = WidePick{i, mode};

@@ -2,10 +2,11 @@
 parts: a one-layer bf16 decoder whose widths leave remainders everywhere
 (d = 4128: 129 k tiles, so steps, parts and folds end in half steps; ffn = 2880;
 vocab = 16048: 1003 column tiles).  By row count (256 CUs) the products take every
-tile shape, unsplit and split or folded, with ragged rows and columns:
-  LM head (STORE)    128 x 128 in 8 parts (17 rows), 192 x 256 in 4 (130), 128 x 256
-                     unsplit (300) and with 3 folded parts (520), 192 x 256 (700,
-                     1500, 2100) and 256 x 256 (2500, 3000) unsplit
+tile shape, unsplit and split, with ragged rows and columns (folded parts: the
+prefill passes below):
+  LM head (STORE)    128 x 128 in 8 parts (17 rows), 192 x 256 in 4 and 3 (130, 520),
+                     128 x 256 (300), 192 x 256 (700, 1500, 2100) and 256 x 256
+                     (2500, 3000) unsplit
   gate/up (SWIGLU)   128 x 128 up to 520 rows, 128 x 256 (700), 192 x 256 (1500,
                      2100, 3000), 256 x 256 (2500)
   O (RESID)          128 x 128 unsplit up to 1500 rows, 192 x 256 (2100, 2500), 256 x
@@ -130,12 +131,14 @@ def test_prefill_passes_keep_the_bits_of_single_chunks(edges):
 def test_prefill_passes_keep_the_history(name):
     """The history rows that a prefill leaves: 1036 tokens in chunks of 128 as one
     pass of 1024 rows and a ragged chunk of 12, against one chunk at a time (limits
-    that leave room for no more).  Of the 25 history rows 13 come from the pass and 12
+    that leave room for no more).  In the bf16 pass q/k/v and O fold 8 parts in one
+    workgroup that single chunks split over eight.  Of the 25 history rows 13 come from the pass and 12
     from the ragged chunk.  A selection reads them all: same record, same caches."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2602_20217_amd import engine as E
-    cfg = dataclasses.replace(CFG if name == "bf16" else W.config("tiny"), L=2)
+    cfg = (dataclasses.replace(CFG, L=2, hq=16, hkv=8) if name == "bf16" else
+           dataclasses.replace(W.config("tiny"), L=2))
     w = W.generate_weights(cfg, seed=0)
     n = 1036
     prompt = W.prompt_ids(cfg.vocab, n)

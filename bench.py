@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 # counter passes (FETCH_SIZE, WRITE_SIZE) scaled by a 256 MiB reference kernel
 # (profiles/decode_kernels_llama8b_ctx8k_counters.txt); valid only while the
 # product's source has the recorded digest
-GATE_UP_TRAFFIC = (235187182, "412febc0e0f969d5f0b24bf37b09bb412af847821cf2f6a5744d5e0c19245aa5")
+GATE_UP_TRAFFIC = (235187182, "c73deb2b583f1e6ca9de6a6c42259621321cccc875dcc0b779786909d4f2f31a")
 
 
 def gate_up_traffic(cfg):
